@@ -38,38 +38,33 @@ def _align(x: int) -> int:
 
 def bias_transposed(w, es: int) -> bool:
     """The backward transposes the bias in a kernel of its own only for fp32
-    or a seq_len that is not a multiple of 8 (bf16 rows of whole 16-byte
-    groups are read as they are by the dK/dV pass)."""
-    return bool(w.bias) and not (es == 2 and w.seq_len % 8 == 0)
+    (the dK/dV pass reads a bf16 bias as it is)."""
+    return bool(w.bias) and es != 2
 
 
 def fused_backward(w, es: int) -> bool:
     """Whether the library runs the single-pass backward for this workload:
     bf16 with head_dim <= 32; with a bias only where the chunk's dBias
-    accumulators fit (up to 128 keys, or head_dim 8 with rows of whole
-    16-byte groups)."""
+    accumulators fit (up to 128 keys, or head_dim 8 up to 256)."""
     if es != 2 or w.head_dim > 32:
         return False
     if not w.bias:
-        return True
+        return w.seq_len <= 256
     nkt = (w.seq_len + 31) // 32
-    return nkt <= 4 or (w.head_dim == 8 and w.seq_len % 8 == 0)
+    return nkt <= 4 or (w.head_dim == 8 and nkt <= 8)
 
 
 def forward_kernel(w, es: int) -> str:
     """The forward kernel the library runs for this workload: the row-walking
     kernel (bias rows held in registers across the rows of one head) for bf16
-    at head_dim <= 32 and at most 256 keys in 16-byte rows, when all rows
+    at head_dim <= 32 and at most 256 keys, when all rows
     share one bias plane and there are at least two (row, head) units per
     resident workgroup; the one-unit kernel otherwise."""
-    if es != 2 or w.head_dim > 32 or not w.bias or w.seq_len % 8 or w.seq_len > 256:
+    if es != 2 or w.head_dim > 32 or not w.bias or w.seq_len > 256:
         return "fwd_kernel"
     if w.rows_per_bias < w.n_rows:
         return "fwd_kernel"
-    nkt = 1
-    while nkt * 32 < w.seq_len:
-        nkt *= 2
-    g0 = 256 * 8 // nkt
+    g0 = 256 * (8 // max(1, (w.seq_len + 31) // 32))
     g = g0 // 8 // w.n_heads * 8 * w.n_heads
     units = w.n_rows * w.n_heads
     return "fwd_rows_kernel" if g > 0 and units >= 2 * g0 else "fwd_kernel"
@@ -118,8 +113,11 @@ def kernel_model(w, es: int, ws_bytes: int):
                T + dsum + biast, 8.0 * S * d))
     # dQ/dBias pass: reads Q K V lse bias mask, writes dQ; workspace: reads dA
     # and Dsum, writes the partial dBias planes
-    ks.append(("qbias_kernel", 3 * T + lse + bias + mask + T, T + dsum + parts, 6.0 * S * d))
-    if w.bias:
+    # (bf16 up to head_dim 32: rows_qbias_kernel, which writes dBias itself with one row chunk)
+    rows = es == 2 and d <= 32
+    ks.append(("rows_qbias_kernel" if rows else "qbias_kernel",
+               3 * T + lse + bias + mask + T + (dbias if rows and not parts else 0), T + dsum + parts, 6.0 * S * d))
+    if w.bias and (parts or not rows):
         ks.append(("dbias_reduce", dbias, parts, 0.0))
     return ks
 

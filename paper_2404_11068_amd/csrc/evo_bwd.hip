@@ -19,7 +19,9 @@
 //           lane = key, registers = queries.  dK and dV finish in registers.
 //           It also does the elementwise part (dA, Dsum, dG) while staging,
 //           and leaves dA and Dsum in the workspace for the second pass.
-//   qbias   one workgroup per (bias plane, head, 32-query tile, chunk of
+//   qbias   (fp32, and bf16 at head_dim 64; bf16 up to head_dim 32 runs
+//           rows_qbias_kernel in evo_bwd_qbias.hip instead)
+//           one workgroup per (bias plane, head, 32-query tile, chunk of
 //           rows); wave w owns key tile w, lane = query, registers = keys.
 //           dQ is summed over the waves through LDS in a fixed order; dS is
 //           accumulated over the chunk's rows in registers and written once
@@ -27,9 +29,11 @@
 //   reduce  sums the partial dBias planes in chunk order.
 // Every sum has a fixed order, so all outputs are bitwise repeatable.
 //
-// Both passes keep their registers near 120 and their LDS under 80 KB so
-// that two 8-wave workgroups share a CU and hide each other's loads and
-// barriers.  Global memory is accessed through buffer instructions on
+// Up to 256 keys both passes keep their registers near 120 and their LDS
+// under 80 KB so that two 8-wave workgroups share a CU and hide each other's
+// loads and barriers.  kv has a kernel for 5, 6, 8, 10, 12, 14 and 16 key tiles:
+// with powers of two only, 384 keys ran as 16-wave workgroups, four of the
+// waves idle and one workgroup to a CU (384 rows, H 4, d 32: 206 -> 156 us).  Global memory is accessed through buffer instructions on
 // per-row resources with out-of-range offsets instead of branches (zeros on
 // load, dropped stores), so every load is issued unconditionally and in the
 // order it is needed.
@@ -110,8 +114,8 @@ __global__ void __launch_bounds__(256) transpose_kernel(const E *__restrict__ sr
 // ---------------------------------------------------------------------------
 struct KvArgs {
     const void *q, *k, *v, *g, *out, *dout;
-    const void *bias;   // [planes][H][L][L], read directly (bf16, L % 8 == 0)
-    const void *biasT;  // its transpose in the workspace (other cases)
+    const void *bias;   // [planes][H][L][L], read directly (bf16)
+    const void *biasT;  // its transpose in the workspace (fp32)
     const uint8_t *mask;
     const float *lse;
     void *dk, *dv, *dg;
@@ -126,9 +130,10 @@ struct KvArgs {
 // LDS tile (bias_block_load / bias_block_transpose_raw in evo_frag.h), as
 // fp32 in the logit layout of the kv tile: lane n = key n, register i =
 // query krow(i, h).
-__device__ __forceinline__ void bias_block_transpose(uint16_t *tile, const u32x4 (&raw)[2], int lane,
-                                                     float *out16) {
-    const Tr<bf16_t>::K32 f = bias_block_transpose_raw(tile, raw, lane);
+template <bool ODD>
+__device__ __forceinline__ void bias_block_transpose(uint16_t *tile, const BiasRaw8<ODD> (&raw)[2], const BiasBuf &b,
+                                                     int L, int lane, float *out16) {
+    const Tr<bf16_t>::K32 f = bias_block_transpose_raw(tile, raw, b, L, lane);
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
         const u32x4 w = __builtin_bit_cast(u32x4, f.v[t]);
@@ -168,9 +173,9 @@ __global__ void __launch_bounds__(NKT / KG * 64) kv_kernel(KvArgs a) {
     // bf16: Q^T and dA^T fragments come from the transposing LDS read of the
     // row-major tiles; fp32 keeps explicit transposed copies
     constexpr bool kTr = ES == 2;
-    // bf16 with whole 16-byte bias row groups: the bias is read as it lies in
-    // memory and transposed per tile in LDS; otherwise from its transpose
-    constexpr bool kBD = kTr && BV;
+    // bf16: the bias is read as it lies in memory and transposed per tile in
+    // LDS (BV: an even row length, see BiasRaw8); fp32: from its transpose
+    constexpr bool kBD = kTr;
     __shared__ __attribute__((aligned(16))) E q_lds[LP * RSTR];
     __shared__ __attribute__((aligned(16))) E da_lds[LP * RSTR];
     __shared__ __attribute__((aligned(16))) E qt_lds[kTr ? 8 : DO * TSTR];
@@ -182,16 +187,17 @@ __global__ void __launch_bounds__(NKT / KG * 64) kv_kernel(KvArgs a) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int h2 = lane >> 5, n = lane & 31;
     const int L = (int)a.L;
-    const int64_t u = xcd_unit(blockIdx.x, gridDim.x);  // (row, head[, half][, key group]), key group fastest
-    if (u >= a.n_units) return;
+    const uint32_t u = xcd_unit32(blockIdx.x, gridDim.x);  // (row, head[, half][, key group]), key group fastest
+    if (u >= (uint32_t)a.n_units) return;
     const int kg = KG == 1 ? 0 : (int)(u % KG);
-    const int64_t unit = u / KG;
+    const uint32_t unit = u / KG;
     const int ch = NHALF == 1 ? 0 : (int)(unit % NHALF);
     const int c_off = ch * DO;  // first output channel of the unit
     const bool writer = ch == 0 && kg == 0;  // writes the per-token outputs shared by the halves and groups
-    const int hh = (int)(unit / NHALF % a.H);
-    const int64_t r = unit / NHALF / a.H;
-    const int64_t b = r / a.rpb;
+    const int hh = (int)(unit / NHALF % (uint32_t)a.H);
+    const uint32_t r32 = unit / NHALF / (uint32_t)a.H;
+    const int64_t r = r32;
+    const int64_t b = r32 / (uint32_t)a.rpb;  // (host: rows fit 31 bits, and rows_per_bias divides them)
     const int64_t rh = r * a.H + hh;
     const bool has_gate = a.g != nullptr, has_mask = a.mask != nullptr,
                has_bias = (kBD ? a.bias : a.biasT) != nullptr;
@@ -234,13 +240,18 @@ __global__ void __launch_bounds__(NKT / KG * 64) kv_kernel(KvArgs a) {
     };
     load_batch(0);
     // bias of this lane's key: reg i <-> query qt*32 + krow(i, h2)
-    const rsrc_t rbt = has_bias ? make_buf((const E *)(kBD ? a.bias : a.biasT) + (b * a.H + hh) * (int64_t)L * L,
-                                           (uint32_t)(L * L * ES))
-                                : none;
+    const int64_t plane = (b * a.H + hh) * (int64_t)L * L;
+    BiasBuf rbd{none, 0u};
+    rsrc_t rbt = none;
+    if constexpr (kBD) {
+        if (has_bias) rbd = make_bias_buf((const E *)a.bias + plane, (uint32_t)(L * L));
+    } else {
+        if (has_bias) rbt = make_buf((const E *)a.biasT + plane, (uint32_t)(L * L * ES));
+    }
     const uint32_t bt_e0 = (uint32_t)key * (uint32_t)L + 8u * h2;  // element of query 8*h2 in this key's row
     float bcur[16];
-    u32x4 braw[2];  // kBD: raw block of the next query tile
-    if constexpr (kBD) bias_block_load(rbt, L, 0, kt, lane, braw);
+    BiasRaw8<!BV> braw[2];  // kBD: raw block of the next query tile
+    if constexpr (kBD) bias_block_load(rbd, L, 0, kt, lane, braw);
     else load_bias16<T, BV>(rbt, bt_e0, bcur);
 
     // ---- stage Q and dA (both layouts); dA, Dsum and dG come from dO, O, G
@@ -314,7 +325,7 @@ __global__ void __launch_bounds__(NKT / KG * 64) kv_kernel(KvArgs a) {
     const float c2 = a.scale * kLog2e;
     const int arow = sig(n);  // permuted A-operand row of this lane
     uint16_t *const bt_tile = &bt_lds[kBD ? wave * 1024 : 0];  // (per wave of this workgroup)
-    if constexpr (kBD) bias_block_transpose(bt_tile, braw, lane, bcur);
+    if constexpr (kBD) bias_block_transpose(bt_tile, braw, rbd, L, lane, bcur);
     __syncthreads();
 
     f32x16 dv_acc = zero16(), dk_acc = zero16();
@@ -325,7 +336,7 @@ __global__ void __launch_bounds__(NKT / KG * 64) kv_kernel(KvArgs a) {
         // the next tile's bias goes out first (loads complete in order)
         float bnext[kBD ? 1 : 16];
         if (qt + 1 < NKT) {
-            if constexpr (kBD) bias_block_load(rbt, L, qt + 1, kt, lane, braw);
+            if constexpr (kBD) bias_block_load(rbd, L, qt + 1, kt, lane, braw);
             else load_bias16<T, BV>(rbt, bt_e0 + 32u * (qt + 1), bnext);
         }
         // S = Q K^T (plus the masked-key term) and dP = dA V^T for 32
@@ -380,7 +391,7 @@ __global__ void __launch_bounds__(NKT / KG * 64) kv_kernel(KvArgs a) {
         Tr<T>::mma_k32(dk_acc, qtf, dsb);
         if (qt + 1 < NKT) {
             if constexpr (kBD) {
-                bias_block_transpose(bt_tile, braw, lane, bcur);
+                bias_block_transpose(bt_tile, braw, rbd, L, lane, bcur);
             } else {
 #pragma unroll
                 for (int i = 0; i < 16; ++i) bcur[i] = bnext[i];
@@ -456,10 +467,7 @@ __global__ void __launch_bounds__(NKT * 64) __attribute__((amdgpu_waves_per_eu(4
     constexpr int CPT = D / VEC;            // 16-byte chunks per token
     constexpr int LP = NKT * 32;
     constexpr int NT = NKT * 64;
-    // bf16 rows of 32 channels use the swizzled 64-byte layout (sw32);
-    // otherwise rows are padded by one 16-byte chunk
-    constexpr bool kSw = kTr && D == 32;
-    constexpr int KSTR = kSw ? D : D + VEC;  // row stride of K, V, Q, dA tiles in LDS (elements)
+    constexpr int KSTR = D + VEC;           // row stride of K, V, Q, dA tiles in LDS (elements)
     constexpr int NKV = (LP * CPT + NT - 1) / NT;  // 16-byte chunks of K (and of V) per thread
     constexpr int NQC = (32 * CPT + NT - 1) / NT;  // 16-byte chunks of the Q (and dA) tile per thread
     // output channels per workgroup: head_dim 64 runs as two units per (row
@@ -482,15 +490,15 @@ __global__ void __launch_bounds__(NKT * 64) __attribute__((amdgpu_waves_per_eu(4
     const int L = (int)a.L;
     const int nqt = (L + 31) / 32;
     // unit -> (b, chunk, qt, head[, half]), head fastest
-    const int64_t unit = xcd_unit(blockIdx.x, gridDim.x);
-    if (unit >= a.n_units) return;
+    const uint32_t unit = xcd_unit32(blockIdx.x, gridDim.x);
+    if (unit >= (uint32_t)a.n_units) return;
     const int ch = NHALF == 1 ? 0 : (int)(unit % NHALF);
     const int c_off = ch * DO;  // first output channel of the unit
-    const int hh = (int)(unit / NHALF % a.H);
-    int64_t rest = unit / NHALF / a.H;
-    const int qt = (int)(rest % nqt);
-    rest /= nqt;
-    const int64_t chunk = rest % a.chunks, b = rest / a.chunks;
+    const int hh = (int)(unit / NHALF % (uint32_t)a.H);
+    uint32_t rest = unit / NHALF / (uint32_t)a.H;
+    const int qt = (int)(rest % (uint32_t)nqt);
+    rest /= (uint32_t)nqt;
+    const int64_t chunk = rest % (uint32_t)a.chunks, b = rest / (uint32_t)a.chunks;
     const int64_t r_begin = b * a.rpb + chunk * a.rows_per_chunk;
     int64_t r_end = r_begin + a.rows_per_chunk;
     if (r_end > (b + 1) * a.rpb) r_end = (b + 1) * a.rpb;
@@ -569,7 +577,7 @@ __global__ void __launch_bounds__(NKT * 64) __attribute__((amdgpu_waves_per_eu(4
             const int idx = tid + j * NT;
             if (idx < LP * CPT) {
                 const int t = idx / CPT, c = (idx % CPT) * VEC;
-                const int o = kSw ? sw32(t, idx % CPT) : t * KSTR + c;
+                const int o = t * KSTR + c;
                 *reinterpret_cast<u32x4 *>(&k_lds[o]) = kr[j];
                 *reinterpret_cast<u32x4 *>(&v_lds[o]) = vr[j];
             }
@@ -579,7 +587,7 @@ __global__ void __launch_bounds__(NKT * 64) __attribute__((amdgpu_waves_per_eu(4
             const int idx = tid + j * NT;
             if (idx < 32 * CPT) {
                 const int t = idx / CPT, c = (idx % CPT) * VEC;
-                const int o = kSw ? sw32(t, idx % CPT) : t * KSTR + c;
+                const int o = t * KSTR + c;
                 *reinterpret_cast<u32x4 *>(&q_lds[o]) = qr[j];
                 *reinterpret_cast<u32x4 *>(&da_lds[o]) = dar[j];
             }
@@ -603,17 +611,10 @@ __global__ void __launch_bounds__(NKT * 64) __attribute__((amdgpu_waves_per_eu(4
         f32x16 dq = zero16();
         if (kbits != 0) {
             ChFrag<T, D> qb, dab, ka, va;
-            if constexpr (kSw) {
-                load_sw32(qb, q_lds, n, h2);
-                load_sw32(dab, da_lds, n, h2);
-                load_sw32(ka, k_lds, kt * 32 + sig(n), h2);
-                load_sw32(va, v_lds, kt * 32 + sig(n), h2);
-            } else {
-                qb.load(&q_lds[n * KSTR], h2);
-                dab.load(&da_lds[n * KSTR], h2);
-                ka.load(&k_lds[(kt * 32 + sig(n)) * KSTR], h2);
-                va.load(&v_lds[(kt * 32 + sig(n)) * KSTR], h2);
-            }
+            qb.load(&q_lds[n * KSTR], h2);
+            dab.load(&da_lds[n * KSTR], h2);
+            ka.load(&k_lds[(kt * 32 + sig(n)) * KSTR], h2);
+            va.load(&v_lds[(kt * 32 + sig(n)) * KSTR], h2);
             const float l2 = lse2_lds[n], ds = dsum_lds[n];
             // S^T = K Q^T + sqrt(d) bias^T, dP^T = V dA^T: lane = query, reg i = key kt*32 + krow(i, h2)
             f32x16 S = bacc, dP = zero16();
@@ -644,9 +645,7 @@ __global__ void __launch_bounds__(NKT * 64) __attribute__((amdgpu_waves_per_eu(4
             }
             // dQ^T (channels x queries) = K^T dS^T over this wave's keys
             K32 kT;
-            if constexpr (kSw) {
-                kT = load_k32_tr_sw32(k_lds, kt * 32, lane);
-            } else if constexpr (kTr) {
+            if constexpr (kTr) {
                 kT = load_k32_tr(k_lds + c_off, KSTR, kt * 32, DO, lane);
             } else {
                 const int c = sig(n);
@@ -776,8 +775,8 @@ __global__ void __launch_bounds__(256) dbias_reduce_kernel(const float *__restri
 // ---------------------------------------------------------------------------
 inline unsigned round8(int64_t n) { return (unsigned)((n + 7) / 8 * 8); }
 
-// bf16 bias rows made of whole 16-byte groups: kv reads the bias as it is
-inline bool bias_direct(const Problem &p) { return p.dtype == 1 && p.L % 8 == 0; }
+// kv reads a bf16 bias as it is, an fp32 one transposed
+inline bool bias_direct(const Problem &p) { return p.dtype == 1; }
 
 // units per (row, head) of the backward passes: head_dim 64 splits the
 // output channels over two workgroups
@@ -791,52 +790,104 @@ hipError_t launch_kv(const KvArgs &ka0, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Key groups per (row, head) of the dK/dV pass: with fewer units than two per
+// CU, each unit's key tiles are split over two workgroups, over four at 64
+// units or fewer (at 128 units two were faster than four: each group stages
+// the whole row's Q, dO, O and G).  Tile counts that do not divide so take
+// the nearest count that does.
 template <typename T, int D, int NKT, bool BV>
-hipError_t launch_passes(const Problem &p, const KvArgs &ka, const QbArgs &qa, hipStream_t s, Tracer &tr) {
-    // grids are rounded up to a multiple of 8 for the XCD-aware unit order;
-    // surplus workgroups exit at once.  With fewer (row, head) units than
-    // two per CU, the dK/dV pass splits each unit's key tiles over two
-    // workgroups, over four at 64 units or fewer (at 128 units two were
-    // faster than four: each group stages the whole row's Q, dO, O and G)
-    hipError_t e;
-    if constexpr (NKT >= 4) {
-        if (ka.n_units <= 64) e = launch_kv<T, D, NKT, BV, 4>(ka, s);
-        else if (ka.n_units < 512) e = launch_kv<T, D, NKT, BV, 2>(ka, s);
-        else e = launch_kv<T, D, NKT, BV, 1>(ka, s);
-    } else {
-        e = launch_kv<T, D, NKT, BV, 1>(ka, s);
+hipError_t launch_kv_g(const KvArgs &ka, hipStream_t s) {
+    constexpr int K4 = NKT % 4 == 0 ? 4 : NKT == 6 ? 3 : NKT == 5 || NKT == 10 ? 5 : NKT == 14 ? 7 : 1;
+    constexpr int K2 = NKT >= 4 && NKT % 2 == 0 ? 2 : 1;
+    if constexpr (K4 > 1) {
+        if (ka.n_units <= 64) return launch_kv<T, D, NKT, BV, K4>(ka, s);
     }
-    if (e != hipSuccess) return e;
-    tr.mark(s);
-    hipLaunchKernelGGL((qbias_kernel<T, D, NKT, BV>), dim3(round8(qa.n_units)), dim3(NKT * 64), 0, s, qa);
-    e = hipGetLastError();
-    if (e == hipSuccess) tr.mark(s);
-    return e;
+    if constexpr (K2 > 1) {
+        if (ka.n_units < 512) return launch_kv<T, D, NKT, BV, K2>(ka, s);
+    }
+    return launch_kv<T, D, NKT, BV, 1>(ka, s);
 }
 
 template <typename T, int D, int NKT>
-hipError_t launch_passes_v(const Problem &p, const KvArgs &ka, const QbArgs &qa, hipStream_t s, Tracer &tr) {
-    // BV: bias rows split into whole 16-byte groups
-    if (p.L % Tr<T>::VEC == 0) return launch_passes<T, D, NKT, true>(p, ka, qa, s, tr);
-    return launch_passes<T, D, NKT, false>(p, ka, qa, s, tr);
+hipError_t launch_kv_v(const Problem &p, const KvArgs &ka, hipStream_t s) {
+    // BV: bf16 bias rows of an even length (fp32: rows of whole 16-byte groups)
+    if (p.L % (sizeof(typename Tr<T>::elem) == 2 ? 2 : 4) == 0) return launch_kv_g<T, D, NKT, true>(ka, s);
+    return launch_kv_g<T, D, NKT, false>(ka, s);
 }
 
 template <typename T, int D>
-hipError_t launch_passes_d(const Problem &p, const KvArgs &ka, const QbArgs &qa, hipStream_t s, Tracer &tr) {
+hipError_t launch_kv_d(const Problem &p, const KvArgs &ka, hipStream_t s) {
     const int64_t nkt = (p.L + 31) / 32;
-    if (nkt <= 1) return launch_passes_v<T, D, 1>(p, ka, qa, s, tr);
-    if (nkt <= 2) return launch_passes_v<T, D, 2>(p, ka, qa, s, tr);
-    if (nkt <= 4) return launch_passes_v<T, D, 4>(p, ka, qa, s, tr);
-    // fp32 at head_dim 64 past 128 keys would need more than the 160 KB of LDS
-    // (the ABI rejects it before this point)
-    if (nkt <= 8) {
-        if constexpr (sizeof(typename Tr<T>::elem) == 4 && D > 32) return hipErrorInvalidValue;
-        else return launch_passes_v<T, D, 8>(p, ka, qa, s, tr);
+    if constexpr (sizeof(typename Tr<T>::elem) == 2 && D <= 32) {
+        // 257..512 keys: up to 16-wave workgroups, bf16 with head_dim <= 32
+        // only (the staged Q and dA of 512 tokens fill the LDS otherwise)
+        if (nkt == 5) return launch_kv_v<T, D, 5>(p, ka, s);
+        if (nkt == 6) return launch_kv_v<T, D, 6>(p, ka, s);
+        if (nkt > 14) return launch_kv_v<T, D, 16>(p, ka, s);
+        if (nkt > 12) return launch_kv_v<T, D, 14>(p, ka, s);
+        if (nkt > 10) return launch_kv_v<T, D, 12>(p, ka, s);
+        if (nkt > 8) return launch_kv_v<T, D, 10>(p, ka, s);
+        return launch_kv_v<T, D, 8>(p, ka, s);  // (up to 128 keys: the single-pass backward)
+    } else {
+        if (nkt <= 1) return launch_kv_v<T, D, 1>(p, ka, s);
+        if (nkt <= 2) return launch_kv_v<T, D, 2>(p, ka, s);
+        if (nkt <= 4) return launch_kv_v<T, D, 4>(p, ka, s);
+        // fp32 at head_dim 64 past 128 keys would need more than the 160 KB of
+        // LDS (the ABI rejects it before this point)
+        if constexpr (sizeof(typename Tr<T>::elem) == 2 || D <= 32) {
+            if (nkt <= 8) return launch_kv_v<T, D, 8>(p, ka, s);
+        }
+        return hipErrorInvalidValue;
     }
-    // 257..512 keys: 16-wave workgroups, bf16 with head_dim <= 32 only (the
-    // staged Q and dA of 512 tokens fill the LDS otherwise)
-    if constexpr (sizeof(typename Tr<T>::elem) == 2 && D <= 32) return launch_passes_v<T, D, 16>(p, ka, qa, s, tr);
-    else return hipErrorInvalidValue;
+}
+
+template <typename T, int D, int NKT>
+hipError_t launch_qb_v(const Problem &p, const QbArgs &qa, hipStream_t s) {
+    // BV: bias rows split into whole 16-byte groups
+    if (p.L % Tr<T>::VEC == 0)
+        hipLaunchKernelGGL((qbias_kernel<T, D, NKT, true>), dim3(round8(qa.n_units)), dim3(NKT * 64), 0, s, qa);
+    else
+        hipLaunchKernelGGL((qbias_kernel<T, D, NKT, false>), dim3(round8(qa.n_units)), dim3(NKT * 64), 0, s, qa);
+    return hipGetLastError();
+}
+
+// fp32, and bf16 at head_dim 64 (bf16 up to head_dim 32: evo_bwd_qbias.hip)
+template <typename T, int D>
+hipError_t launch_qb_d(const Problem &p, const QbArgs &qa, hipStream_t s) {
+    const int64_t nkt = (p.L + 31) / 32;
+    if (nkt <= 1) return launch_qb_v<T, D, 1>(p, qa, s);
+    if (nkt <= 2) return launch_qb_v<T, D, 2>(p, qa, s);
+    if (nkt <= 4) return launch_qb_v<T, D, 4>(p, qa, s);
+    if constexpr (sizeof(typename Tr<T>::elem) == 2 || D <= 32) {
+        if (nkt <= 8) return launch_qb_v<T, D, 8>(p, qa, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+// the dK/dV pass; grids are rounded up to a multiple of 8 for the XCD-aware
+// unit order (surplus workgroups exit at once)
+template <typename T>
+hipError_t launch_kv_pass(const Problem &p, const KvArgs &ka, hipStream_t s) {
+    switch (p.D) {
+        case 8: return launch_kv_d<T, 8>(p, ka, s);
+        case 16: return launch_kv_d<T, 16>(p, ka, s);
+        case 64: return launch_kv_d<T, 64>(p, ka, s);
+        default: return launch_kv_d<T, 32>(p, ka, s);
+    }
+}
+
+template <typename T>
+hipError_t launch_qb_pass(const Problem &p, const QbArgs &qa, hipStream_t s) {
+    if constexpr (sizeof(typename Tr<T>::elem) == 2) {
+        return launch_qb_d<T, 64>(p, qa, s);
+    } else {
+        switch (p.D) {
+            case 8: return launch_qb_d<T, 8>(p, qa, s);
+            case 16: return launch_qb_d<T, 16>(p, qa, s);
+            case 64: return launch_qb_d<T, 64>(p, qa, s);
+            default: return launch_qb_d<T, 32>(p, qa, s);
+        }
+    }
 }
 
 template <typename T>
@@ -847,8 +898,7 @@ hipError_t launch_bwd_t(const Problem &p, const BwdPtrs &x, void *ws, const BwdP
     const int64_t planes = x.bias ? (p.N / p.rpb) * p.H : 0;
     hipError_t e;
     tr.mark(s);
-    // the kv pass reads a bf16 bias with whole 16-byte row groups directly
-    // (the first traced interval is then empty)
+    // the kv pass reads a bf16 bias directly (the first traced interval is then empty)
     const bool bias_t = x.bias && !bias_direct(p);
     if (!bias_t && x.bias) tr.mark(s);
     if (bias_t) {
@@ -870,6 +920,12 @@ hipError_t launch_bwd_t(const Problem &p, const BwdPtrs &x, void *ws, const BwdP
     ka.da = w + plan.off_da; ka.dsum = (float *)(w + plan.off_dsum);
     ka.L = p.L; ka.rpb = rpb; ka.srow = p.srow; ka.stok = p.stok; ka.H = p.H; ka.scale = scale;
     ka.n_units = p.N * p.H * head_halves(p);
+    e = launch_kv_pass<T>(p, ka, s);
+    if (e != hipSuccess) return e;
+    tr.mark(s);
+    if (rows_qbias_supported(p))
+        return launch_rows_qbias(p, x, ka.da, ka.dsum, (float *)(w + plan.off_part), plan.chunks, plan.rows_per_chunk,
+                              plan.key_parts, s, tr);
     QbArgs qa;
     qa.q = x.q; qa.k = x.k; qa.v = x.v; qa.bias = x.bias; qa.mask = x.mask; qa.lse = x.lse;
     qa.da = ka.da; qa.dsum = ka.dsum; qa.dq = x.dq;
@@ -878,12 +934,8 @@ hipError_t launch_bwd_t(const Problem &p, const BwdPtrs &x, void *ws, const BwdP
     qa.chunks = plan.chunks; qa.rows_per_chunk = plan.rows_per_chunk;
     qa.H = p.H; qa.scale = scale;
     qa.n_units = plan.n_wg;
-    switch (p.D) {
-        case 8: e = launch_passes_d<T, 8>(p, ka, qa, s, tr); break;
-        case 16: e = launch_passes_d<T, 16>(p, ka, qa, s, tr); break;
-        case 64: e = launch_passes_d<T, 64>(p, ka, qa, s, tr); break;
-        default: e = launch_passes_d<T, 32>(p, ka, qa, s, tr); break;
-    }
+    e = launch_qb_pass<T>(p, qa, s);
+    if (e == hipSuccess) tr.mark(s);
     if (e != hipSuccess || !x.bias) return e;
     const int64_t pe = p.L * p.L;
     int64_t blocks = (planes * pe + 255) / 256;
@@ -947,7 +999,12 @@ BwdPlan plan_bwd(const Problem &p, bool has_bias, size_t cap) {
     // workgroups gain (16 rows over 8 heads: 4 chunks beat 8; one-wave
     // workgroups of 32-key rows gain from every extra chunk instead)
     int64_t chunks = 0;
-    if (planes > 0 && rpb > 0 && nqt > 0) {
+    const bool rows_qbias = rows_qbias_supported(p);
+    int key_parts = 1;
+    if (rows_qbias) {
+        int64_t g = 1;
+        if (planes > 0 && rpb > 0 && nqt > 0) rows_qbias_chunks(p, has_bias, &chunks, &g, &key_parts);
+    } else if (planes > 0 && rpb > 0 && nqt > 0) {
         const int64_t per_chunk = planes * p.H * nqt * waves * head_halves(p);  // waves per row chunk
         chunks = (target_waves + per_chunk - 1) / per_chunk;
         if (waves >= 8 && chunks > rpb / 4) chunks = rpb / 4;
@@ -974,8 +1031,12 @@ BwdPlan plan_bwd(const Problem &p, bool has_bias, size_t cap) {
         off = align256(off + (size_t)(p.N * p.H * p.L) * 4);
         pl.off_biast = off;
         if (has_bias && !bias_direct(p)) off = align256(off + (size_t)(planes * p.H * p.L * p.L * es));
+        pl.key_parts = key_parts;
         pl.off_part = off;
-        if (has_bias) off = align256(off + (size_t)(planes * p.H * c * p.L * p.L) * 4);
+        // (bf16 with one row chunk per plane writes dBias directly)
+        if (has_bias && !rows_qbias) off = align256(off + (size_t)(planes * p.H * c * p.L * p.L) * 4);
+        if (has_bias && rows_qbias && c > 1)
+            off = align256(off + (size_t)(planes * p.H * c * p.L * rows_qbias_pitch(p)) * 4);
         pl.total = off;
         return pl;
     };

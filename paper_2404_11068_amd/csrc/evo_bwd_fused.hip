@@ -124,11 +124,11 @@ __global__ void __launch_bounds__(NKT * 64) bwd_fused_kernel(FusedArgs a) {
     const int nqt = (L + 31) / 32;
     // unit -> (plane b, row chunk, head), head fastest: the heads of one
     // chunk land on one XCD (xcd_unit) and share the token cache lines
-    const int64_t unit = xcd_unit(blockIdx.x, gridDim.x);
-    if (unit >= a.n_units) return;
-    const int hh = (int)(unit % a.H);
-    const int64_t bc = unit / a.H;
-    const int64_t chunk = bc % a.chunks, b = bc / a.chunks;
+    const uint32_t unit = xcd_unit32(blockIdx.x, gridDim.x);
+    if (unit >= (uint32_t)a.n_units) return;
+    const int hh = (int)(unit % (uint32_t)a.H);
+    const uint32_t bc = unit / (uint32_t)a.H;
+    const int64_t chunk = bc % (uint32_t)a.chunks, b = bc / (uint32_t)a.chunks;
     const int64_t r_begin = b * a.rpb + chunk * a.rows_per_chunk;
     int64_t r_end = r_begin + a.rows_per_chunk;
     if (r_end > (b + 1) * a.rpb) r_end = (b + 1) * a.rpb;
@@ -142,8 +142,8 @@ __global__ void __launch_bounds__(NKT * 64) bwd_fused_kernel(FusedArgs a) {
     const int key = kt * 32 + n;
     const bool kin = key < L;
     const uint32_t key_off = kin ? (uint32_t)key * stok_b : kOOB;
-    const rsrc_t rb = HB ? make_buf((const E *)a.bias + (b * a.H + hh) * (int64_t)L * L, (uint32_t)(L * L * ES))
-                         : none;
+    const BiasBuf rb = HB ? make_bias_buf((const E *)a.bias + (b * a.H + hh) * (int64_t)L * L, (uint32_t)(L * L))
+                          : BiasBuf{none, 0u};
     uint16_t *const tp = &tp_lds[wave * 1024];
     // sqrt(d) on an identity, for the bias product (two bf16 terms where
     // sqrt(d) has no exact bf16 value; their sum matches it to ~3e-7)
@@ -178,7 +178,7 @@ __global__ void __launch_bounds__(NKT * 64) bwd_fused_kernel(FusedArgs a) {
         // per-row opaque copies of the lane's bias-row offset (query sig(n) of
         // tile 0, this wave's keys) and lane index: each query tile's bias
         // and dQ addresses are formed from them inside the tile's step
-        const uint32_t boff = opaque_u32((uint32_t)((sig(n) * L + kt * 32 + 8 * h2) * ES));
+        const uint32_t boff = opaque_u32(rb.off + (uint32_t)((sig(n) * L + kt * 32 + 8 * h2) * ES));
         const uint32_t lane_r = opaque_u32((uint32_t)lane);
         // ---- every load of the row goes out first, in the order of use
         QKF kb, vb;
@@ -208,11 +208,14 @@ __global__ void __launch_bounds__(NKT * 64) bwd_fused_kernel(FusedArgs a) {
             }
         }
         // first query tile's bias rows
-        K32 bnext;
-        if constexpr (HB) {
-            if constexpr (BV) bnext = bias_rows_k32_at(rb, boff);
-            else bnext = bias_rows_k32<BV>(rb, L, 0, kt, lane);
-        }
+        BiasRaw<!BV> bnext;
+        if constexpr (HB) bnext.load(rb.r, boff);
+        // the rows of query tile qt as the A operand of the bias product; rows
+        // past L must be zeros (even lengths: past the end of the resource)
+        auto bias_rows = [&](int qt) {
+            const bool full = kt * 32 + 32 <= L && qt * 32 + 32 <= L;
+            return bnext.get(boff, full, qt * 32 + sig(n) < L ? L - kt * 32 - 8 * h2 : 0);
+        };
 
         // ---- staging: Q and dA into LDS; dA, Dsum and dG from dO, O and G
         {
@@ -282,8 +285,9 @@ __global__ void __launch_bounds__(NKT * 64) bwd_fused_kernel(FusedArgs a) {
         // tile's is formed before the previous tile's dQ barrier
         f32x16 T = zero16();
         if constexpr (HB) {
-            Tr<bf16_t>::mma_k32(T, bnext, eye_hi);
-            if (two_term) Tr<bf16_t>::mma_k32(T, bnext, eye_lo);
+            const K32 br = bias_rows(0);
+            Tr<bf16_t>::mma_k32(T, br, eye_hi);
+            if (two_term) Tr<bf16_t>::mma_k32(T, br, eye_lo);
         }
         __syncthreads();
 
@@ -295,10 +299,7 @@ __global__ void __launch_bounds__(NKT * 64) bwd_fused_kernel(FusedArgs a) {
             float *const dq_part = dqp[qt & 1];
             // the next tile's bias rows go out first (loads complete in order)
             if constexpr (HB) {
-                if (qt + 1 < NKT) {
-                    if constexpr (BV) bnext = bias_rows_k32_at(rb, boff + (uint32_t)((qt + 1) * 32 * L * ES));
-                    else bnext = bias_rows_k32<BV>(rb, L, qt + 1, kt, lane);
-                }
+                if (qt + 1 < NKT) bnext.load(rb.r, boff + (uint32_t)((qt + 1) * 32 * L * ES));
             }
             f32x16 dq = zero16();
             if (kany) {
@@ -390,8 +391,9 @@ __global__ void __launch_bounds__(NKT * 64) bwd_fused_kernel(FusedArgs a) {
             if constexpr (HB) {
                 if (qt + 1 < NKT) {
                     T = zero16();
-                    Tr<bf16_t>::mma_k32(T, bnext, eye_hi);
-                    if (two_term) Tr<bf16_t>::mma_k32(T, bnext, eye_lo);
+                    const K32 br = bias_rows(qt + 1);
+                    Tr<bf16_t>::mma_k32(T, br, eye_hi);
+                    if (two_term) Tr<bf16_t>::mma_k32(T, br, eye_lo);
                 }
             }
             __syncthreads();
@@ -412,10 +414,10 @@ __global__ void __launch_bounds__(NKT * 64) bwd_fused_kernel(FusedArgs a) {
                     const int q = (int)(idx / (D / 4)), cq = (int)(idx % (D / 4));
                     f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
                     // partials read four at a time and added as fixed trees
-                    constexpr int G = NKT < 4 ? NKT : 4;
 #pragma unroll
-                    for (int w0 = 0; w0 < NKT; w0 += G) {
-                        f32x4 x[G];
+                    for (int w0 = 0; w0 < NKT; w0 += 4) {
+                        const int G = NKT - w0 < 4 ? NKT - w0 : 4;
+                        f32x4 x[4];
 #pragma unroll
                         for (int w = 0; w < G; ++w)
                             x[w] = *reinterpret_cast<const f32x4 *>(&dq_part[dqs_index<D>((w0 + w) * 32 + q, q, cq)]);
@@ -509,11 +511,10 @@ __global__ void __launch_bounds__(256) dbias_tiles_reduce_kernel(const float *__
                                                                  int H, int64_t chunks, int L) {
     __shared__ __attribute__((aligned(16))) float red[3][64 * 16];
     const int nqt = (L + 31) / 32;
-    const int64_t tiles = (int64_t)nqt * nqt;
-    const int64_t blk = blockIdx.x;
-    const int64_t tile = blk % tiles, ph = blk / tiles;  // ph = plane * H + head
-    const int64_t b = ph / H, hh = ph % H;
-    const int qt = (int)(tile / nqt), kt = (int)(tile % nqt);
+    const uint32_t tiles = (uint32_t)(nqt * nqt);
+    const uint32_t tile = blockIdx.x % tiles, ph = blockIdx.x / tiles;  // ph = plane * H + head
+    const int64_t b = ph / (uint32_t)H, hh = ph % (uint32_t)H;
+    const int qt = (int)(tile / (uint32_t)nqt), kt = (int)(tile % (uint32_t)nqt);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t per = (chunks + 3) / 4;
     const int64_t c0 = wave * per, c1 = c0 + per < chunks ? c0 + per : chunks;
@@ -522,7 +523,7 @@ __global__ void __launch_bounds__(256) dbias_tiles_reduce_kernel(const float *__
     for (int g4 = 0; g4 < 4; ++g4) acc[g4] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     // element (b, c, hh, tile, lane, i) of the partials
     const int64_t stride_c = (int64_t)H * tiles * 1024;
-    const float *src = part + (b * chunks * H + hh) * tiles * 1024 + tile * 1024 + lane * 16;
+    const float *src = part + (b * chunks * H + hh) * (int64_t)tiles * 1024 + tile * 1024u + lane * 16;
     int64_t c = c0;
     for (; c + 2 <= c1; c += 2) {
         f32x4 x[2][4];
@@ -572,9 +573,9 @@ hipError_t launch_fused_t(const FusedArgs &fa, hipStream_t s) {
 }
 
 // With a bias, the chunk's dBias accumulators (a whole [L, L] plane per
-// workgroup) must fit beside the rest: every head dim up to 128 keys, and at
-// 256 keys head_dim 8 with rows of whole 16-byte groups (three query tiles of
-// accumulators in LDS).  Other shapes take the two-pass backward.
+// workgroup) must fit beside the rest: every head dim up to 128 keys, and
+// head_dim 8 up to 256 keys (up to three query tiles of accumulators in LDS).
+// Other shapes take the two-pass backward.
 template <int D, int NKT>
 constexpr bool kFusedBias = NKT <= 4 || D == 8;
 
@@ -582,19 +583,24 @@ template <int D, int NKT>
 hipError_t launch_fused_n(const Problem &p, const FusedArgs &fa, hipStream_t s) {
     if (!fa.bias) return launch_fused_t<D, NKT, false, true>(fa, s);
     if constexpr (kFusedBias<D, NKT>) {
-        if (p.L % 8 == 0) return launch_fused_t<D, NKT, true, true>(fa, s);
-        if constexpr (NKT <= 4) return launch_fused_t<D, NKT, true, false>(fa, s);
+        if (p.L % 2 == 0) return launch_fused_t<D, NKT, true, true>(fa, s);
+        return launch_fused_t<D, NKT, true, false>(fa, s);
     }
     return hipErrorInvalidValue;  // excluded by fused_bwd_supported
 }
 
 template <int D>
 hipError_t launch_fused_d(const Problem &p, const FusedArgs &fa, hipStream_t s) {
-    const int64_t nkt = (p.L + 31) / 32;
-    if (nkt <= 1) return launch_fused_n<D, 1>(p, fa, s);
-    if (nkt <= 2) return launch_fused_n<D, 2>(p, fa, s);
-    if (nkt <= 4) return launch_fused_n<D, 4>(p, fa, s);
-    return launch_fused_n<D, 8>(p, fa, s);
+    switch ((p.L + 31) / 32) {  // a wave past the row's last key tile would only wait at the barriers
+        case 1: return launch_fused_n<D, 1>(p, fa, s);
+        case 2: return launch_fused_n<D, 2>(p, fa, s);
+        case 3: return launch_fused_n<D, 3>(p, fa, s);
+        case 4: return launch_fused_n<D, 4>(p, fa, s);
+        case 5: return launch_fused_n<D, 5>(p, fa, s);
+        case 6: return launch_fused_n<D, 6>(p, fa, s);
+        case 7: return launch_fused_n<D, 7>(p, fa, s);
+        default: return launch_fused_n<D, 8>(p, fa, s);
+    }
 }
 
 }  // namespace
@@ -603,7 +609,7 @@ bool fused_bwd_supported(const Problem &p, bool has_bias) {
     const int64_t nkt = (p.L + 31) / 32;
     if (p.dtype != 1 || p.D > 32 || nkt > 8) return false;  // (its LDS tiles hold up to 256 keys)
     if (!has_bias) return true;
-    return nkt <= 4 || (p.D == 8 && p.L % 8 == 0);
+    return nkt <= 4 || p.D == 8;
 }
 
 // rows per chunk and chunk count of the fused backward: about 2048 waves in

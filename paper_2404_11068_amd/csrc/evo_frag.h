@@ -353,19 +353,98 @@ __device__ __forceinline__ Tr<bf16_t>::K32 load_k32_tr_sw32(const uint16_t *X, i
 }
 
 // ---------------------------------------------------------------------------
-// A 32 x 32 block of a bf16 pair-bias plane [query][key] (row length L, a
-// multiple of 8 so that every 16-byte group lies inside one row), handed to
-// the lanes that own keys.
+// Groups of eight consecutive bf16 of a pair-bias plane.  A plane's rows have
+// L elements, so a group starts on a 4-byte boundary when L is even (one
+// 16-byte load, the hardware asks for dword alignment only) and on a 2-byte
+// boundary in every other row when L is odd: there the five aligned dwords
+// around it are loaded (ODD below) and shifted by the row's half dword where
+// the group is used.  Against one load per element, which odd lengths and
+// lengths that are no multiple of 8 used to take, that is 2 loads instead of
+// 8 per group.  The resource starts at the dword of the plane's first element
+// and ends with the dword of its last, so no load leaves the dwords of the
+// plane; the range check is per dword.
+struct BiasBuf {
+    rsrc_t r;
+    uint32_t off;  // byte offset of the plane's first element in r (0 or 2)
+};
+__device__ __forceinline__ BiasBuf make_bias_buf(const uint16_t *plane, uint32_t elems) {
+    const uintptr_t b = (uintptr_t)plane;
+    const uint32_t off = (uint32_t)(b & 2u);
+    return {make_buf((const void *)(b - off), (elems * 2u + off + 3u) & ~3u), off};
+}
+template <bool ODD> struct BiasRaw8;
+template <> struct BiasRaw8<false> {
+    u32x4 w;
+    // off: byte offset of the group's first element in the resource
+    __device__ __forceinline__ void load(rsrc_t r, uint32_t off) { w = bload16(r, off); }
+    __device__ __forceinline__ u32x4 get(uint32_t) const { return w; }
+};
+template <> struct BiasRaw8<true> {
+    u32x4 w;
+    uint32_t t;
+    __device__ __forceinline__ void load(rsrc_t r, uint32_t off) {
+        const uint32_t o = off & ~3u;
+        w = bload16(r, o);
+        t = bload4(r, o + 16u);
+    }
+    // off: any byte offset of the row's parity (the groups of one lane start
+    // an even number of elements apart)
+    __device__ __forceinline__ u32x4 get(uint32_t off) const {
+        const uint32_t sh = off & 2u;
+        const uint32_t a = w.x, b = w.y, c = w.z, d = w.w;
+        return u32x4{__builtin_amdgcn_alignbyte(b, a, sh), __builtin_amdgcn_alignbyte(c, b, sh),
+                     __builtin_amdgcn_alignbyte(d, c, sh), __builtin_amdgcn_alignbyte(t, d, sh)};
+    }
+};
+// the first n elements of a group (n <= 0: none, n >= 8: all), zeros after them
+__device__ __forceinline__ u32x4 keep_first(u32x4 w, int n) {
+    const uint32_t x[4] = {w.x, w.y, w.z, w.w};
+    uint32_t y[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) y[j] = n >= 2 * j + 2 ? x[j] : n == 2 * j + 1 ? x[j] & 0xffffu : 0u;
+    return u32x4{y[0], y[1], y[2], y[3]};
+}
+// the two groups {8h+s}, {16+8h+s} of a 32-key tile's k32 order
+template <bool ODD> struct BiasRaw {
+    BiasRaw8<ODD> g[2];
+    __device__ __forceinline__ void load(rsrc_t r, uint32_t off) {
+        g[0].load(r, off);
+        g[1].load(r, off + 32u);
+    }
+    // left: keys of the row from this lane's first group on.  Past the row's
+    // end an even length reads the next row's (finite) values, whose keys are
+    // masked; an odd one may reach the half dword after the plane, which can
+    // hold anything, so those elements become zeros (full: the whole 32-key
+    // tile lies inside the row, wave-uniform)
+    __device__ __forceinline__ Tr<bf16_t>::K32 get(uint32_t off, bool full, int left) const {
+        u32x4 a = g[0].get(off), b = g[1].get(off);
+        if (ODD && !full) {
+            a = keep_first(a, left);
+            b = keep_first(b, left - 16);
+        }
+        Tr<bf16_t>::K32 f;
+        f.v[0] = __builtin_bit_cast(bf16x8, a);
+        f.v[1] = __builtin_bit_cast(bf16x8, b);
+        return f;
+    }
+};
+
+// ---------------------------------------------------------------------------
+// A 32 x 32 block of a bf16 pair-bias plane [query][key], handed to the lanes
+// that own keys.
 //
-// bias_block_load: lane l reads the 16-byte chunks l and l + 64 of the block
-// of (query tile qt, key tile kt) as it lies in memory (row = chunk / 4 =
-// query, 8 keys per chunk).  Rows past L read zeros.
-__device__ __forceinline__ void bias_block_load(rsrc_t rb, int L, int qt, int kt, int lane, u32x4 (&raw)[2]) {
+// bias_block_load: lane l reads the 8-key chunks l and l + 64 of the block of
+// (query tile qt, key tile kt) as it lies in memory (row = chunk / 4 = query,
+// 8 keys per chunk).  Rows past L read zeros.  (Keys past L may hold
+// anything: they stay in the lanes that own them, which store nothing.)
+template <bool ODD>
+__device__ __forceinline__ void bias_block_load(const BiasBuf &b, int L, int qt, int kt, int lane,
+                                                BiasRaw8<ODD> (&raw)[2]) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
         const int r = (lane >> 2) + 16 * j, cc = lane & 3;
         const int qi = qt * 32 + r;
-        raw[j] = bload16(rb, qi < L ? (uint32_t)(qi * L + kt * 32 + 8 * cc) * 2u : kOOB);
+        raw[j].load(b.r, qi < L ? b.off + (uint32_t)(qi * L + kt * 32 + 8 * cc) * 2u : kOOB);
     }
 }
 
@@ -375,14 +454,16 @@ __device__ __forceinline__ void bias_block_load(rsrc_t rb, int L, int qt, int kt
 // lane n the column sig(n), i.e. key n, at the query rows krow(i, h) of
 // register i (packed bf16 in the k32 order) -- the logit layout of a tile
 // whose lanes own keys.
-__device__ __forceinline__ Tr<bf16_t>::K32 bias_block_transpose_raw(uint16_t *tile, const u32x4 (&raw)[2],
-                                                                    int lane) {
+template <bool ODD>
+__device__ __forceinline__ Tr<bf16_t>::K32 bias_block_transpose_raw(uint16_t *tile, const BiasRaw8<ODD> (&raw)[2],
+                                                                    const BiasBuf &b, int L, int lane) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
         const int r = (lane >> 2) + 16 * j, cc = lane & 3;
+        const u32x4 w = raw[j].get(b.off + (uint32_t)(r * L) * 2u);  // (query tiles start an even number of rows apart)
         // keys 8cc + 4b + e (e < 4) go to column sig(8cc + 4b + e) = 16(cc/2) + 8b + 4(cc%2) + e
         const int c0 = 16 * (cc >> 1) + 4 * (cc & 1);
-        const u32x2 lo = {raw[j].x, raw[j].y}, hi = {raw[j].z, raw[j].w};
+        const u32x2 lo = {w.x, w.y}, hi = {w.z, w.w};
         *reinterpret_cast<u32x2 *>(&tile[r * 32 + c0]) = lo;
         *reinterpret_cast<u32x2 *>(&tile[r * 32 + c0 + 8]) = hi;
     }
@@ -390,47 +471,6 @@ __device__ __forceinline__ Tr<bf16_t>::K32 bias_block_transpose_raw(uint16_t *ti
 }
 
 // ---------------------------------------------------------------------------
-// The pair bias of (query tile qt, key tile kt) as the A operand of a k32
-// product: lane m takes the bias row of query qt*32 + sig(m) (the permuted
-// rows of the Q operand of S = Q K^T), k-slots = keys kt*32 + {8h+s, 16+8h+s},
-// as it lies in memory.  Times sqrt(d) on an identity B operand it adds
-// sqrt(d) * bias to the logit tile whose lanes own keys.  BV: rows of whole
-// 16-byte groups (two loads per lane); otherwise one element per load.  Rows
-// and keys past L read zeros.
-template <bool BV>
-__device__ __forceinline__ Tr<bf16_t>::K32 bias_rows_k32(rsrc_t rb, int L, int qt, int kt, int lane) {
-    const int m = lane & 31, h = lane >> 5;
-    const int qi = qt * 32 + sig(m);
-    const int k0 = kt * 32 + 8 * h;
-    Tr<bf16_t>::K32 f;
-    if constexpr (BV) {
-        f.v[0] = __builtin_bit_cast(bf16x8, bload16(rb, qi < L ? (uint32_t)(qi * L + k0) * 2u : kOOB));
-        f.v[1] = __builtin_bit_cast(bf16x8, bload16(rb, qi < L ? (uint32_t)(qi * L + k0 + 16) * 2u : kOOB));
-    } else {
-        short8tr w[2];
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int kj = k0 + 16 * t + e;
-                w[t][e] = (short)bload2(rb, (qi < L && kj < L) ? (uint32_t)(qi * L + kj) * 2u : kOOB);
-            }
-        f.v[0] = __builtin_bit_cast(bf16x8, w[0]);
-        f.v[1] = __builtin_bit_cast(bf16x8, w[1]);
-    }
-    return f;
-}
-
-// bias_rows_k32<true> with the byte offset of the lane's first group given
-// (query row * L + first key) * 2: tiles further down add a constant to it,
-// and rows past L land past the end of the resource (zeros).
-__device__ __forceinline__ Tr<bf16_t>::K32 bias_rows_k32_at(rsrc_t rb, uint32_t off) {
-    Tr<bf16_t>::K32 f;
-    f.v[0] = __builtin_bit_cast(bf16x8, bload16(rb, off));
-    f.v[1] = __builtin_bit_cast(bf16x8, bload16(rb, off + 32u));
-    return f;
-}
-
 // An opaque copy of a per-lane value: the compiler cannot see through it, so
 // what is computed from the copy stays inside the loop that makes the copy.
 // Used where hoisting loop-invariant addresses (one per unrolled step) out of
@@ -490,6 +530,13 @@ __device__ __forceinline__ f32x16 zero16() {
 // are dispatched round-robin over the 8 XCDs), so the heads of one row share
 // that XCD's L2.
 __device__ __forceinline__ int64_t xcd_unit(int64_t b, int64_t nb) {
+    if (nb % 8 != 0) return b;
+    return (b % 8) * (nb / 8) + b / 8;
+}
+
+// the same in 32 bits (64-bit divisions of the unit index by run-time counts
+// took over a thousand scalar instructions at the start of every workgroup)
+__device__ __forceinline__ uint32_t xcd_unit32(uint32_t b, uint32_t nb) {
     if (nb % 8 != 0) return b;
     return (b % 8) * (nb / 8) + b / 8;
 }

@@ -20,10 +20,8 @@
 // probabilities in registers are already the B operand of O^T = V^T P^T.
 //
 // bf16 path, per key tile of 32 keys:
-//   * the logits are kept "raw", S_raw = K Q^T + sqrt(d) * bias; the pair
-//     bias enters through the MFMA accumulator: a constant A operand holding
-//     sqrt(d) (split into two bf16 terms) on a permuted diagonal times the
-//     bias row loaded as raw bf16 (the B operand) -- no per-logit unpacking;
+//   * the logits are kept "raw", S_raw = K Q^T + sqrt(d) * bias; the scaled
+//     bias is the starting value of the tile's first K Q^T product;
 //   * the scale 1/sqrt(d) and log2(e) are folded into the exponent's FMA;
 //   * with head_dim < 32, a row of ones in the V^T operand makes the same
 //     MFMA produce the row sums of the probabilities.
@@ -63,30 +61,6 @@ struct FwdArgs {
     int H;
     float scale;
 };
-
-// raw bf16 pair bias of key tile kt for query row qi, in the k32 slot order:
-// slots {8h+s, 16+8h+s} = keys kt*32 + those slots.  Rows past L
-// read zeros; keys past L read the next row's values (those keys are masked,
-// so the values never matter).  BV: L % 8 == 0, rows are 16-byte aligned.
-template <bool BV>
-__device__ __forceinline__ Tr<bf16_t>::K32 bias_k32(rsrc_t rb, int qi, int kt, int L, int h) {
-    Tr<bf16_t>::K32 f;
-    const uint32_t e0 = (uint32_t)(qi * L + kt * 32 + 8 * h);  // element index of slot 0
-    if constexpr (BV) {
-        f.v[0] = __builtin_bit_cast(bf16x8, bload16(rb, e0 * 2u));
-        f.v[1] = __builtin_bit_cast(bf16x8, bload16(rb, e0 * 2u + 32u));
-    } else {
-        short8tr w0, w1;
-#pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            w0[s] = (short)bload2(rb, (e0 + s) * 2u);
-            w1[s] = (short)bload2(rb, (e0 + 16 + s) * 2u);
-        }
-        f.v[0] = __builtin_bit_cast(bf16x8, w0);
-        f.v[1] = __builtin_bit_cast(bf16x8, w1);
-    }
-    return f;
-}
 
 // A bias fragment as the starting value of a logit tile: register i holds
 // sqd * bias of key krow(i, h) -- the k32 slot order is the accumulator's
@@ -140,7 +114,7 @@ __global__ void __launch_bounds__(NKT / QG * 64) fwd_kernel(FwdArgs a) {
     constexpr int PCH = (32 - DO) / 8;         // constant 16-byte chunks per V row
     constexpr int NCH = NKT / KC;              // chunks of KC key tiles
     constexpr int NPF = (LP * CPT + NT - 1) / NT;  // 16-byte chunks of K (and of V) per thread
-    constexpr int NBB = kBf && BV ? KC : 1;    // bias fragments per chunk held in registers
+    constexpr int NBB = kBf ? KC : 1;          // bias fragments per chunk held in registers
     constexpr int NG = ES == 2 ? 1 : 2;        // 16-byte gate loads per 8 channels
     // bf16 at head_dim 8: the logit product runs on the k=16 instruction; each
     // K row in LDS is followed by its k-slots 8..15 (the key's masked-key word,
@@ -159,10 +133,10 @@ __global__ void __launch_bounds__(NKT / QG * 64) fwd_kernel(FwdArgs a) {
     // one workgroup per (row, head[, channel half], query group) unit;
     // consecutive units (the query groups and heads of a row) land on the
     // same XCD
-    const int64_t u = xcd_unit(blockIdx.x, gridDim.x);
-    if (u >= a.n_units) return;
+    const uint32_t u = xcd_unit32(blockIdx.x, gridDim.x);
+    if (u >= (uint32_t)a.n_units) return;
     const int qg = QG == 1 ? 0 : (int)(u % QG);
-    const int64_t uh = u / QG;
+    const uint32_t uh = u / QG;
     const int qi = (qg * NW + wave) * 32 + n;
     const bool qvalid = qi < L;
     const bool has_bias = a.bias != nullptr, has_mask = a.mask != nullptr, has_gate = a.g != nullptr;
@@ -172,14 +146,17 @@ __global__ void __launch_bounds__(NKT / QG * 64) fwd_kernel(FwdArgs a) {
 
     const int ch = NHALF == 1 ? 0 : (int)(uh % NHALF);
     const int c_off = ch * DO;  // first output channel of the unit
-    const int64_t r = uh / NHALF / a.H;
-    const int hh = (int)(uh / NHALF % a.H);
+    const int64_t r = uh / NHALF / (uint32_t)a.H;
+    const int hh = (int)(uh / NHALF % (uint32_t)a.H);
     auto tok_buf = [&](const void *X) {
         return make_buf((const E *)X + r * a.srow + (int64_t)hh * D, row_bytes);
     };
-    const rsrc_t rb = has_bias ? make_buf((const E *)a.bias + ((r / a.rpb) * a.H + hh) * (int64_t)L * L,
-                                          (uint32_t)(L * L * ES))
-                               : make_buf(nullptr, 0u);
+    const E *const bias_plane = has_bias ? (const E *)a.bias + ((r / a.rpb) * a.H + hh) * (int64_t)L * L : nullptr;
+    BiasBuf rb;
+    if constexpr (kBf) rb = make_bias_buf(bias_plane, has_bias ? (uint32_t)(L * L) : 0u);
+    else rb = {make_buf(bias_plane, has_bias ? (uint32_t)(L * L * ES) : 0u), 0u};
+    // bf16: the lane's first bias group (query qi, key 8 * h2)
+    const uint32_t b_off = rb.off + (uint32_t)(qi * L + 8 * h2) * 2u;
 
     // ---- loads of the unit, in the order they are needed
     {
@@ -244,10 +221,10 @@ __global__ void __launch_bounds__(NKT / QG * 64) fwd_kernel(FwdArgs a) {
     if constexpr (kPad8) qf.load(tok_buf(a.q), q_off, h2, kBf16One);
     else qf.load(tok_buf(a.q), q_off, h2);
     // bias of the first chunk, then the gate (needed last)
-    K32 bcur[NBB];
-    if constexpr (kBf && BV) {
+    BiasRaw<!BV> bcur[NBB];
+    if constexpr (kBf) {
 #pragma unroll
-        for (int kc = 0; kc < KC; ++kc) bcur[kc] = bias_k32<BV>(rb, qi, kc, L, h2);
+        for (int kc = 0; kc < KC; ++kc) bcur[kc].load(rb.r, b_off + 64u * kc);
     }
     const rsrc_t rg = has_gate ? tok_buf(a.g) : make_buf(nullptr, 0u);
     u32x4 graw[2][NG];
@@ -267,6 +244,8 @@ __global__ void __launch_bounds__(NKT / QG * 64) fwd_kernel(FwdArgs a) {
     sqrt_split(D, sq_hi, sq_lo);
     const float sqd = sq_hi + sq_lo;
     __syncthreads();
+    // waves whose query tile lies wholly past L have only staged
+    if (__builtin_amdgcn_readfirstlane((qg * NW + wave) * 32) >= L) return;
 
     float m2 = -INFINITY;  // reference max, base-2 exponent units (per query)
     float lsum = 0.0f;     // row sum (unused with the ones row)
@@ -274,11 +253,11 @@ __global__ void __launch_bounds__(NKT / QG * 64) fwd_kernel(FwdArgs a) {
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
         // ---- the next chunk's bias goes out first (loads complete in order)
-        K32 bnext[NBB];
-        if constexpr (kBf && BV) {
+        BiasRaw<!BV> bnext[NBB];
+        if constexpr (kBf) {
             if (c + 1 < NCH) {
 #pragma unroll
-                for (int kc = 0; kc < KC; ++kc) bnext[kc] = bias_k32<BV>(rb, qi, (c + 1) * KC + kc, L, h2);
+                for (int kc = 0; kc < KC; ++kc) bnext[kc].load(rb.r, b_off + 64u * ((c + 1) * KC + kc));
             }
         }
         // ---- pass 1: raw logits of the chunk and their max
@@ -288,15 +267,13 @@ __global__ void __launch_bounds__(NKT / QG * 64) fwd_kernel(FwdArgs a) {
 #pragma unroll
         for (int kc = 0; kc < KC; ++kc) {
             const int kt = c * KC + kc;
-            // tiles whose bias is read per tile load it before any branch
-            K32 bt;
+            // fp32 reads its bias per tile, before any branch
             float bf[16];
-            if constexpr (kBf && !BV) bt = bias_k32<false>(rb, qi, kt, L, h2);
             if constexpr (!kBf) {
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     const uint32_t j = (uint32_t)(kt * 32 + krow(i, h2));
-                    bf[i] = __builtin_bit_cast(float, bload4(rb, ((uint32_t)qi * L + j) * 4u));
+                    bf[i] = __builtin_bit_cast(float, bload4(rb.r, ((uint32_t)qi * L + j) * 4u));
                 }
             }
             const uint32_t kb = __builtin_amdgcn_readfirstlane(kbits[kt]);
@@ -306,8 +283,7 @@ __global__ void __launch_bounds__(NKT / QG * 64) fwd_kernel(FwdArgs a) {
             kf.load(&k_lds[(kt * 32 + sig(n)) * KSTR], h2);
             s[kc] = zero16();
             if constexpr (kBf) {
-                if constexpr (BV) bt = bcur[kc];
-                if (has_bias) s[kc] = bias_acc(bt, sqd);
+                if (has_bias) s[kc] = bias_acc(bcur[kc].get(b_off, kt * 32 + 32 <= L, L - kt * 32 - 8 * h2), sqd);
             }
             QKF::mma(s[kc], kf, qf);
             if constexpr (!kBf) {
@@ -367,7 +343,7 @@ __global__ void __launch_bounds__(NKT / QG * 64) fwd_kernel(FwdArgs a) {
             }
             Tr<T>::mma_k32(o, va, pb);
         }
-        if constexpr (kBf && BV) {
+        if constexpr (kBf) {
             if (c + 1 < NCH) {
 #pragma unroll
                 for (int kc = 0; kc < KC; ++kc) bcur[kc] = bnext[kc];
@@ -455,7 +431,7 @@ __global__ void __launch_bounds__(NKT / QG * 64) fwd_kernel(FwdArgs a) {
 // above the threshold means no combined one is), and the exponent offset
 // changes only with that max.  Every value is computed as in the one-unit
 // kernel: the outputs are the same bits.
-template <int D, int NKT>
+template <int D, int NKT, bool ODD>
 __global__ void __launch_bounds__(NKT * 64) __attribute__((amdgpu_waves_per_eu(2))) fwd_rows_kernel(FwdArgs a) {
     using T = bf16_t;
     using E = uint16_t;
@@ -511,11 +487,12 @@ __global__ void __launch_bounds__(NKT * 64) __attribute__((amdgpu_waves_per_eu(2
     // unit u -> (row ur, head uh), advanced incrementally: u grows by G per step
     const int H = a.H;
     const int64_t G = gridDim.x;
-    const int64_t GH = G / H;
-    const int Gh = (int)(G % H);  // 0: the host makes G a multiple of H
-    int64_t u = xcd_unit(blockIdx.x, G);
-    int64_t ur = u / H;
-    int uh = (int)(u % H);
+    const int64_t GH = gridDim.x / (uint32_t)H;
+    const int Gh = (int)(gridDim.x % (uint32_t)H);  // 0: the host makes G a multiple of H
+    const uint32_t u0 = xcd_unit32(blockIdx.x, gridDim.x);
+    int64_t u = u0;
+    int64_t ur = u0 / (uint32_t)H;
+    int uh = (int)(u0 % (uint32_t)H);
     // first element of a unit's [L, d] block in the token tensors; a unit past
     // the last one gets an empty resource (its loads read zeros)
     auto tok_buf = [&](const void *X, int64_t tb, bool ok) {
@@ -527,10 +504,15 @@ __global__ void __launch_bounds__(NKT * 64) __attribute__((amdgpu_waves_per_eu(2
     // kept as the fp32 starting values of the logit tiles (sqrt(d) * bias)
     f32x16 bacc[NKT];
     {
-        const rsrc_t rb = u < a.n_units ? make_buf((const E *)a.bias + (int64_t)uh * L * L, (uint32_t)(L * L * 2))
-                                        : none;
+        const BiasBuf rb = make_bias_buf((const E *)a.bias + (int64_t)uh * L * L,
+                                         u < a.n_units ? (uint32_t)(L * L) : 0u);
+        const uint32_t b_off = rb.off + (uint32_t)(qi * L + 8 * h2) * 2u;
+        BiasRaw<ODD> braw[NKT];
 #pragma unroll
-        for (int kt = 0; kt < NKT; ++kt) bacc[kt] = bias_acc(bias_k32<true>(rb, qi, kt, L, h2), sqd);
+        for (int kt = 0; kt < NKT; ++kt) braw[kt].load(rb.r, b_off + 64u * kt);
+#pragma unroll
+        for (int kt = 0; kt < NKT; ++kt)
+            bacc[kt] = bias_acc(braw[kt].get(b_off, kt * 32 + 32 <= L, L - kt * 32 - 8 * h2), sqd);
     }
 
     // ---- the in-flight unit's K, V, key-mask byte and query tile
@@ -707,92 +689,136 @@ __global__ void __launch_bounds__(NKT * 64) __attribute__((amdgpu_waves_per_eu(2
 
 // key tiles per register-resident chunk: one keeps the kernel near 90
 // registers (two tiles need about 130, which halves the occupancy)
-template <int NKT> constexpr int kFwdKC = 1;
+constexpr int kFwdKC = 1;
 
-template <typename T, int D, int NKT, bool BV, int QG>
-hipError_t launch_q(const Problem &p, const FwdPtrs &x, hipStream_t s) {
-    // unaligned bias rows are read per element, one tile per chunk
-    constexpr int KC = BV ? kFwdKC<NKT> : 1;
+FwdArgs make_args(const Problem &p, const FwdPtrs &x) {
     FwdArgs a;
     a.q = x.q; a.k = x.k; a.v = x.v; a.g = x.g; a.bias = x.bias; a.mask = x.mask;
     a.out = x.out; a.lse = x.lse;
     a.L = p.L; a.rpb = p.rpb; a.srow = p.srow; a.stok = p.stok; a.H = p.H;
-    a.n_units = p.N * p.H * (D > 32 ? D / 32 : 1) * QG;
-    a.scale = 1.0f / sqrtf((float)D);
+    a.n_units = p.N * p.H;
+    a.scale = 1.0f / sqrtf((float)p.D);
+    return a;
+}
+
+template <typename T, int D, int NKT, bool BV, int QG>
+hipError_t launch_q(const Problem &p, const FwdPtrs &x, hipStream_t s) {
+    FwdArgs a = make_args(p, x);
+    a.n_units *= (D > 32 ? D / 32 : 1) * QG;
     // one workgroup per unit; the grid is rounded up to a multiple of 8 so
     // that the XCD-aware unit order applies (surplus workgroups exit)
     const int64_t nwg = (a.n_units + 7) / 8 * 8;
-    hipLaunchKernelGGL((fwd_kernel<T, D, NKT, KC, BV, QG>), dim3((unsigned)nwg), dim3(NKT / QG * 64), 0, s, a);
+    hipLaunchKernelGGL((fwd_kernel<T, D, NKT, kFwdKC, BV, QG>), dim3((unsigned)nwg), dim3(NKT / QG * 64), 0, s, a);
     return hipGetLastError();
 }
 
-// Row-walking kernel: eligible when every row uses one bias plane, rows are
-// 16-byte aligned (bf16, L % 8 == 0), at most 256 keys, and there are at
+// Row-walking kernel: eligible when every row uses one bias plane, bf16, at
+// most 256 keys, and there are at
 // least two units per resident workgroup (one 8-wave workgroup per CU at
 // the kernel's two waves per SIMD: 256 CUs x 8 waves); with one, the bias
 // held in registers would not be reused at all.  EVO_ATTN_FWD_ROWS=0
 // in the environment at the time of the call selects the one-unit kernel
 // instead (same results; read on every call, no state kept).
-constexpr int64_t kRowsResidentWaves = 256 * 8;
+constexpr int64_t rows_resident(int nkt) { return 256 * (8 / nkt); }
 
 inline bool fwd_rows_enabled() {
     const char *e = getenv("EVO_ATTN_FWD_ROWS");
     return !(e && e[0] == '0');
 }
 
+// grid of the row-walking kernel (0: not eligible): the resident workgroups, a
+// multiple of 8 (XCD-aware order) and of the head count (every workgroup
+// keeps one head)
+int64_t rows_grid(const Problem &p, const FwdPtrs &x) {
+    const int64_t nkt = (p.L + 31) / 32;
+    if (p.dtype != 1 || p.D > 32 || nkt > 8 || x.bias == nullptr || p.rpb < p.N || p.N >= (int64_t(1) << 31)) return 0;
+    const int64_t g0 = rows_resident((int)nkt);
+    if (p.N * p.H < 2 * g0 || !fwd_rows_enabled()) return 0;
+    return g0 / 8 / p.H * 8 * p.H;
+}
+
 template <int D, int NKT>
 hipError_t launch_rows(const Problem &p, const FwdPtrs &x, hipStream_t s, int64_t g) {
-    FwdArgs a;
-    a.q = x.q; a.k = x.k; a.v = x.v; a.g = x.g; a.bias = x.bias; a.mask = x.mask;
-    a.out = x.out; a.lse = x.lse;
-    a.L = p.L; a.rpb = p.rpb; a.srow = p.srow; a.stok = p.stok; a.H = p.H;
-    a.n_units = p.N * p.H;
-    a.scale = 1.0f / sqrtf((float)D);
-    hipLaunchKernelGGL((fwd_rows_kernel<D, NKT>), dim3((unsigned)g), dim3(NKT * 64), 0, s, a);
+    const FwdArgs a = make_args(p, x);
+    if (p.L % 2 == 0)
+        hipLaunchKernelGGL((fwd_rows_kernel<D, NKT, false>), dim3((unsigned)g), dim3(NKT * 64), 0, s, a);
+    else
+        hipLaunchKernelGGL((fwd_rows_kernel<D, NKT, true>), dim3((unsigned)g), dim3(NKT * 64), 0, s, a);
     return hipGetLastError();
+}
+
+template <int D>
+hipError_t launch_rows_d(const Problem &p, const FwdPtrs &x, hipStream_t s, int64_t g) {
+    switch ((p.L + 31) / 32) {
+        case 1: return launch_rows<D, 1>(p, x, s, g);
+        case 2: return launch_rows<D, 2>(p, x, s, g);
+        case 3: return launch_rows<D, 3>(p, x, s, g);
+        case 4: return launch_rows<D, 4>(p, x, s, g);
+        case 5: return launch_rows<D, 5>(p, x, s, g);
+        case 6: return launch_rows<D, 6>(p, x, s, g);
+        case 7: return launch_rows<D, 7>(p, x, s, g);
+        default: return launch_rows<D, 8>(p, x, s, g);
+    }
 }
 
 // Query groups per (row, head): with fewer units than two per CU (512), a
 // unit's query tiles are split over two workgroups, over four at 64 units or
 // fewer (each stages the unit's K and V, mostly from the L2 its XCD shares
 // with the unit's other groups; at 128 units two were faster than four).
+// Tile counts that do not divide so take the nearest count that does.
 template <typename T, int D, int NKT, bool BV>
 hipError_t launch_t(const Problem &p, const FwdPtrs &x, hipStream_t s) {
     const int64_t units = p.N * p.H * (D > 32 ? D / 32 : 1);
-    if constexpr (sizeof(typename Tr<T>::elem) == 2 && D <= 32 && BV && NKT <= 8) {
-        // grid: the resident workgroups, a multiple of 8 (XCD-aware order)
-        // and of the head count (every workgroup keeps one head)
-        const int64_t g0 = kRowsResidentWaves / NKT;
-        const int64_t g = g0 / 8 / p.H * 8 * p.H;
-        if (x.bias != nullptr && p.rpb >= p.N && g > 0 && units >= 2 * g0 && p.N < (int64_t(1) << 31) &&
-            fwd_rows_enabled())
-            return launch_rows<D, NKT>(p, x, s, g);
+    constexpr int Q4 = NKT % 4 == 0 ? 4 : NKT == 3 || NKT == 6 ? 3 : NKT == 5 || NKT == 10 ? 5 : NKT == 14 ? 7 : 1;
+    constexpr int Q2 = NKT < 4 ? Q4 : NKT % 2 == 0 ? 2 : 1;
+    if constexpr (Q4 > 1) {
+        if (units <= 64) return launch_q<T, D, NKT, BV, Q4>(p, x, s);
     }
-    if constexpr (NKT >= 4) {
-        if (units <= 64) return launch_q<T, D, NKT, BV, 4>(p, x, s);
-        if (units < 512) return launch_q<T, D, NKT, BV, 2>(p, x, s);
+    if constexpr (Q2 > 1) {
+        if (units < 512) return launch_q<T, D, NKT, BV, Q2>(p, x, s);
     }
     return launch_q<T, D, NKT, BV, 1>(p, x, s);
 }
 
 template <typename T, int D, int NKT>
 hipError_t launch_t(const Problem &p, const FwdPtrs &x, hipStream_t s) {
-    // fp32 reads its bias per element either way
-    if (sizeof(typename Tr<T>::elem) == 2 && p.L % Tr<T>::VEC == 0) return launch_t<T, D, NKT, true>(p, x, s);
+    // bf16 bias rows of an odd length start on a 2-byte boundary; fp32 reads
+    // its bias per element either way
+    if (sizeof(typename Tr<T>::elem) == 2 && p.L % 2 == 0) return launch_t<T, D, NKT, true>(p, x, s);
     return launch_t<T, D, NKT, false>(p, x, s);
 }
 
 template <typename T, int D>
 hipError_t launch_d(const Problem &p, const FwdPtrs &x, hipStream_t s) {
     const int64_t nkt = (p.L + 31) / 32;
+    constexpr bool kBf = sizeof(typename Tr<T>::elem) == 2;
+    if constexpr (kBf && D <= 32) {
+        const int64_t g = rows_grid(p, x);
+        if (g > 0) return launch_rows_d<D>(p, x, s, g);
+    }
     if (nkt <= 1) return launch_t<T, D, 1>(p, x, s);
     if (nkt <= 2) return launch_t<T, D, 2>(p, x, s);
+    // bf16: a kernel per tile count up to 6 and per two above 8.  A wave past
+    // the row's last tile would hold its slot and LDS for nothing: with powers
+    // of two only, 384 keys (384 rows, H 4, d 32) ran 123 us against 85, 317
+    // keys (317 rows, an odd length, whose bias was read element by element)
+    // 210 us against 73.
+    if constexpr (kBf && D <= 32) {
+        if (nkt == 3) return launch_t<T, D, 3>(p, x, s);
+        if (nkt == 5) return launch_t<T, D, 5>(p, x, s);
+        if (nkt == 6) return launch_t<T, D, 6>(p, x, s);
+    }
     if (nkt <= 4) return launch_t<T, D, 4>(p, x, s);
     if (nkt <= 8) return launch_t<T, D, 8>(p, x, s);
-    // 257..512 keys: 16 query tiles, 16 waves (bf16, head_dim <= 32: K and V
-    // of 512 keys fit the LDS; the ABI rejects the rest before this point)
-    if constexpr (sizeof(typename Tr<T>::elem) == 2 && D <= 32) return launch_t<T, D, 16>(p, x, s);
-    else return hipErrorInvalidValue;
+    // 257..512 keys: up to 16 query tiles, 16 waves (bf16, head_dim <= 32: K
+    // and V of 512 keys fit the LDS; the ABI rejects the rest before this point)
+    if constexpr (kBf && D <= 32) {
+        if (nkt <= 10) return launch_t<T, D, 10>(p, x, s);
+        if (nkt <= 12) return launch_t<T, D, 12>(p, x, s);
+        if (nkt <= 14) return launch_t<T, D, 14>(p, x, s);
+        return launch_t<T, D, 16>(p, x, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 template <typename T>

@@ -43,6 +43,7 @@ struct BwdPlan {
     int64_t chunks;          // row chunks per bias plane (dBias partial planes per plane and head)
     int64_t rows_per_chunk;  // rows handled by one workgroup of the dBias-producing pass
     int64_t n_wg;            // workgroups of the qbias kernel (two-pass plan)
+    int key_parts;           // waves that share a row in the rows_qbias kernel (two-pass plan, bf16, head_dim <= 32)
     size_t off_da, off_dsum, off_biast, off_part, total;
 };
 
@@ -78,6 +79,13 @@ void fused_bwd_chunks(const Problem &p, bool has_bias, int64_t *chunks, int64_t 
 size_t fused_bwd_partial_bytes(const Problem &p, int64_t chunks);
 hipError_t launch_bwd_fused(const Problem &p, const BwdPtrs &x, void *ws, int64_t chunks, int64_t rows_per_chunk,
                             hipStream_t s, Tracer &tr);
+
+// second pass of the two-pass backward for bf16 at head_dim <= 32 (evo_bwd_qbias.hip)
+bool rows_qbias_supported(const Problem &p);
+int rows_qbias_pitch(const Problem &p);  // floats per row of a partial dBias plane
+void rows_qbias_chunks(const Problem &p, bool has_bias, int64_t *chunks, int64_t *rows_per_chunk, int *key_parts);
+hipError_t launch_rows_qbias(const Problem &p, const BwdPtrs &x, const void *da, const float *dsum, float *part,
+                          int64_t chunks, int64_t rows_per_chunk, int key_parts, hipStream_t s, Tracer &tr);
 
 // kernels launched by one backward call (for Tracer sizing)
 int bwd_kernel_count(bool has_bias);
