@@ -70,7 +70,7 @@ int evo_ln_proj_fwd_ex(const evo_proj_dims *dims, const void *x, const float *ln
  * forward's normalised input) and upstream gradients douts[p] ([R, HD] bf16,
  * a HOST array of n_proj device pointers):
  *
- *   dY       = sum_p douts[p] @ weight[p*HD:(p+1)*HD, :]   rounded to bf16
+ *   dY       = sum_p douts[p] @ weight[p*HD:(p+1)*HD, :]   (fp32)
  *   dx, dln_weight, dln_bias = LayerNorm backward of dY (as evo_layernorm_bwd,
  *              from x, ln_weight and the forward's mean, rstd)
  *   dweight[p*HD + f, c] = sum_t douts[p][t, f] * y[t, c]   (fp32)

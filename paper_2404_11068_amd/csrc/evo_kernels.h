@@ -154,11 +154,11 @@ struct PjBwdArgs {
 
 struct PjBwdPlan {
     int64_t n_chunks, chunk_tokens;   // token chunks of the weight-gradient pass
-    size_t off_dy, off_ln, off_dw, off_db, total;
+    size_t off_ln, off_dw, off_db, total;
 };
 
 // ln == false: a plain linear layer (no LayerNorm; lnw, mean, rstd, dlnw,
-// dlnb null and y = x), dY written straight to dx
+// dlnb null and y = x), dY written to dx as it is
 PjBwdPlan plan_proj_bwd(int64_t R, int C, int HD, int P, bool ln = true);
 hipError_t launch_ln_proj_bwd(const PjBwdArgs &a, void *ws, const PjBwdPlan &plan, hipStream_t s);
 

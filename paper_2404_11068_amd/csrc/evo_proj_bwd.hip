@@ -5,7 +5,7 @@
 // dout_p of the P projections:
 //
 //   dY      = sum_p dout_p W_p          [R, C]   (dy_kernel, MFMA)
-//   dx, dln = LayerNorm backward of dY           (the LayerNorm kernels)
+//   dx, dln = LayerNorm backward of dY           (dy_kernel's epilogue)
 //   dW_p    = dout_p^T y                [HD, C]  (dw_kernel, MFMA, per token chunk)
 //   dbias_p = sum over tokens of dout_p          (same kernel, a ones operand)
 //
@@ -13,8 +13,7 @@
 // both products the contraction runs along an axis that is not contiguous in
 // one operand (features of W in dY, tokens in dW), so those operands are
 // staged in LDS and read with the transposing LDS read (ds_read_b64_tr_b16),
-// which yields the MFMA fragment directly.  dY is rounded to bf16 (the
-// gradient precision between the layers) before the LayerNorm backward.
+// which yields the MFMA fragment directly.
 #include <stdlib.h>
 
 #include "evo_frag.h"
@@ -56,6 +55,19 @@ inline int proj_bwd_fb(int C, int HD, int P) {
     return 32;
 }
 
+// tokens per workgroup of the dY pass: 128, fewer (down to eight 32 x 32 tiles,
+// one per wave) while the workgroups would leave CUs idle.  At 128 channels
+// always 64: with 128, two workgroups no longer share a CU (100000 tokens x 128:
+// backward 88.5 -> 79.6 us, as a plain layer 44.7 -> 39.5); at 256 channels 64
+// would read the weight twice as often (32768 x 256: 77.5 against 69.8 us).
+inline int dy_block_tokens(int64_t R, int C) {
+    const int least = C >= 256 ? 32 : C >= 128 ? 64 : 128;
+    if (C == 128) return 64;
+    int tm = 128;
+    while (tm > least && (R + tm - 1) / tm < 256) tm /= 2;
+    return tm;
+}
+
 // a wave-uniform pointer, moved to scalar registers
 __device__ __forceinline__ const char *uniform_ptr(const char *p) {
     const uint64_t v = (uint64_t)p;
@@ -68,128 +80,136 @@ __device__ __forceinline__ const void *dout_ptr(const PjBwdArgs &a, int p) {
 }
 
 // ---------------------------------------------------------------------------
-// dY tile of 128 tokens x C channels with NW = 16 waves (8 for C = 64).
-// Output tiles (token tile tb, channel tile ct): wave w takes tb = w % 4 and
-// ct = w / 4 + (NW / 4) j.  The contraction runs over stages of 64 features;
-// both operands of a stage go through LDS (double-buffered): the dout rows
-// [128 tokens][64 features], read back as row fragments, and the weight rows
-// [64 features][C], read back with the transposing read.  Global loads of a
-// stage are issued four stages ahead into a ring of register stages, in one
-// in-order stream (the memory counter retires loads in issue order, so a
-// wait for one load is a wait for every older one).
-// A workgroup covers CW of the C channels (CW < C splits the channels over
-// blockIdx.y when there are too few token blocks to fill the GPU).
-template <int CW>
+// dY of TM tokens x all C channels per workgroup of eight waves, and with a
+// LayerNorm its backward in the epilogue: dx of the tokens and one partial row
+// of dln_w | dln_b.  The waves form a WT x WC grid over the tokens and channels,
+// MT x MC tiles of 32 x 32 each (two by two at 128 tokens x 256 channels: a
+// fragment read from LDS then serves two products).  The contraction runs over
+// stages of 64 features; both operands of a stage go through LDS
+// (double-buffered): the dout rows [TM][64], 16-byte chunk c of row r at
+// c ^ akey(r), read back as row fragments, and the weight rows [64][C], read
+// back with the transposing read.  Global loads are issued four stages ahead
+// into a ring of register stages, in one in-order stream (the memory counter
+// retires loads in issue order, so a wait for one load is a wait for every
+// older one).
+//
+// The LayerNorm epilogue takes dY through LDS in fp32 to whole rows (C/8 lanes a row),
+// so it is not rounded to bf16 on its way into the LayerNorm backward, and
+// neither dY (33 MB written and read at 32768 x 256) nor a second kernel is
+// left.  32768 x 256, F 1024 (kernel trace, minima): dY 32.3 + LayerNorm
+// backward 11.7 + its reduction 3.9 us -> 36.6 us; the whole backward 80.6 -> 70 us.
+template <int C, int TM>
 struct DyCfg {
-    static constexpr int NW = CW >= 128 ? 16 : 8;
-    static constexpr int NT = 64 * NW;
+    static constexpr int NW = 8, NT = 64 * NW, KC = 64;
+    static constexpr int TT = TM / 32, CT = C / 32;
+    static constexpr int WT = CT >= 8 ? (TT >= 4 ? 2 : 1) : CT == 4 ? 2 : 4;  // token groups of waves
+    static constexpr int WC = NW / WT;
+    static constexpr int MT = TT / WT, MC = CT / WC;
+    static_assert(MT >= 1 && MC >= 1 && MT * WT == TT && MC * WC == CT, "wave grid");
+    static constexpr int WSTR = C + kLdsPad;      // weight stage row stride (elements)
+    static constexpr int LW = KC * WSTR, LA = TM * KC;
+    static constexpr int OSTR = C + 4;            // row stride of the fp32 dY tile (floats)
+    static constexpr int NRED = 2 * C * NW;       // dln partials of the waves (floats)
+    static constexpr int LDS_STAGE = 2 * (LW + LA) * 2, LDS_OUT = (TM * OSTR + NRED) * 4;
+    template <bool LN> static constexpr int LDS = !LN || LDS_STAGE > LDS_OUT ? LDS_STAGE : LDS_OUT;
 };
 
-template <int C, int CW>
-__global__ __launch_bounds__(DyCfg<CW>::NT) void dy_kernel(PjBwdArgs a, void *__restrict__ dy) {
-    constexpr int NW = DyCfg<CW>::NW, NT = DyCfg<CW>::NT;
-    constexpr int TM = 128, KC = 64, NR = 4;
-    constexpr int NCT = CW / 32, CG = NW / 4, TPW = NCT / CG;  // channel tiles per wave
-    static_assert(TPW >= 1 && NCT % CG == 0 && C % CW == 0, "dy_kernel takes C = 64, 128, 256");
-    constexpr int WSTR = CW + kLdsPad;        // weight stage row stride (elements)
-    // dout stage row stride: 36 dwords, so 16 lanes on 16 consecutive rows and
-    // one 16-byte column hit 16 distinct groups of four banks
-    constexpr int ASTR = KC + 8;
-    constexpr int NA = TM * KC / 8 / NT;      // dout 16-byte chunks per thread and stage
-    constexpr int NWL = KC * CW / 8 / NT;     // weight 16-byte chunks per thread and stage
-    constexpr int OSTR = 40;                  // staging row stride (elements) of a 32x32 output tile
-    constexpr int LW = KC * WSTR, LA = TM * ASTR;
-    constexpr int LT = 2 * (LW + LA), LS = NW * 32 * OSTR;
-    static_assert(NA >= 1 && NWL >= 1 && NA * NT == TM * KC / 8 && NWL * NT == KC * CW / 8, "stage split");
-    __shared__ __attribute__((aligned(16))) uint16_t lds[LT > LS ? LT : LS];
+// Chunk swizzle of the dout rows (128 bytes, eight 16-byte chunks): reading one
+// chunk of 16 consecutive rows, and writing four chunks of four consecutive
+// rows (consecutive lanes on one row's 64 bytes, so that a load's lanes share
+// cache lines), touch every bank once.
+__device__ __forceinline__ int akey(int r) {
+    const int j = (r >> 1) & 7;
+    return ((j & 1) << 2) | (j >> 1);
+}
+
+// v from another lane of the same 16-lane row, chosen by a DPP control word
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
+}
+// sum over LPR consecutive lanes (8, 16 or 32), left in each of them
+template <int LPR>
+__device__ __forceinline__ float row_sum(float v) {
+    v += dpp<0xB1>(v);                               // quad_perm [1,0,3,2]
+    v += dpp<0x4E>(v);                               // quad_perm [2,3,0,1]
+    v += dpp<0x141>(v);                              // row_half_mirror
+    if constexpr (LPR >= 16) v += dpp<0x140>(v);     // row_mirror
+    if constexpr (LPR >= 32) v += __shfl_xor(v, 16, 64);
+    return v;
+}
+
+template <int C, int TM, bool LN, int NR>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void dy_kernel(PjBwdArgs a,
+                                                                                     float *__restrict__ part_ln) {
+    using G = DyCfg<C, TM>;
+    constexpr int NT = G::NT, KC = G::KC, MT = G::MT, MC = G::MC, WSTR = G::WSTR;
+    constexpr int NA = (TM * KC / 8 + NT - 1) / NT;  // dout 16-byte chunks per thread and stage
+    constexpr int NWL = KC * C / 8 / NT;             // weight 16-byte chunks per thread and stage
+    static_assert(NWL * NT == KC * C / 8, "stage split");
+    __shared__ __attribute__((aligned(16))) char lds[G::template LDS<LN>];
+    uint16_t *const st = (uint16_t *)lds;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 31, h = lane >> 5;
-    const int tb = wave & 3, cg = wave >> 2;
+    const int wt = wave / G::WC, wc = wave % G::WC;
     const int64_t row0 = (int64_t)blockIdx.x * TM;
     int64_t nrows = a.R - row0;
     nrows = nrows < TM ? nrows : TM;
     const int F = a.P * a.HD;
     const int NS = (F + KC - 1) / KC;
     const rsrc_t rW = make_buf(a.W, (uint32_t)F * C * 2u);
-    const int c0 = blockIdx.y * CW;          // first channel of this workgroup
 
-    // dout chunk j of this thread: k32 step (half) hf of the stage, token row
-    // r, 16-byte column c4; a wave covers 16 rows x 4 columns of one half
-    // (one projection), 16 lanes per column
+    // dout chunk j of this thread: half hf of the stage (32 features, all in
+    // one projection), token row r, 16-byte column c4 of the half
     int a_r[NA], a_c4[NA], a_hf[NA];
 #pragma unroll
     for (int j = 0; j < NA; ++j) {
         const int idx = tid + j * NT;
-        a_hf[j] = idx >> 9;
-        const int ii = idx & 511;
-        a_r[j] = (ii >> 6) * 16 + (ii & 15);
-        a_c4[j] = (ii >> 4) & 3;
+        a_hf[j] = __builtin_amdgcn_readfirstlane(idx / (TM * 4));
+        const int ii = idx % (TM * 4);
+        a_r[j] = ii >> 2;
+        a_c4[j] = ii & 3;
     }
-    // per-half cursor over the projections (wave-uniform, in scalar registers:
-    // a per-lane copy would turn every load into a loop over distinct
-    // resources): projection pointer, its successors, feature offset
     const uint32_t ablk = (uint32_t)nrows * a.HD * 2u;
     const int64_t aoff = row0 * a.HD * 2;
-    const char *dp0 = (const char *)a.dout0 + aoff, *dp1 = (const char *)a.dout1 + aoff;
-    const char *dp2 = (const char *)a.dout2 + aoff, *dp3 = (const char *)a.dout3 + aoff;
-    const char *cur[NA], *nx1[NA], *nx2[NA], *nx3[NA];
-    int lp[NA], lfl[NA];
-#pragma unroll
-    for (int j = 0; j < NA; ++j) {
-        // k32 step a_hf[j] of stage 0: feature 32 a_hf[j]
-        const int f = 32 * a_hf[j];
-        const int p0 = __builtin_amdgcn_readfirstlane(f / a.HD);
-        lfl[j] = __builtin_amdgcn_readfirstlane(f % a.HD);
-        lp[j] = p0;
-        cur[j] = uniform_ptr(p0 == 0 ? dp0 : p0 == 1 ? dp1 : p0 == 2 ? dp2 : dp3);
-        nx1[j] = uniform_ptr(p0 == 0 ? dp1 : p0 == 1 ? dp2 : dp3);
-        nx2[j] = uniform_ptr(p0 == 0 ? dp2 : dp3);
-        nx3[j] = dp3;
-    }
-    auto advance = [&](int j) {  // by one stage (64 features = two k32 steps)
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            lfl[j] += 32;
-            const bool wrap = lfl[j] == a.HD;
-            lfl[j] = __builtin_amdgcn_readfirstlane(wrap ? 0 : lfl[j]);
-            lp[j] = __builtin_amdgcn_readfirstlane(wrap ? lp[j] + 1 : lp[j]);
-            cur[j] = uniform_ptr(wrap ? nx1[j] : cur[j]);
-            nx1[j] = uniform_ptr(wrap ? nx2[j] : nx1[j]);
-            nx2[j] = uniform_ptr(wrap ? nx3[j] : nx2[j]);
-        }
-    };
     auto load_stage = [&](int s, u32x4 (&ra)[NA], u32x4 (&rw)[NWL]) {
 #pragma unroll
         for (int j = 0; j < NA; ++j) {
-            const rsrc_t ro = make_buf(cur[j], __builtin_amdgcn_readfirstlane(lp[j] < a.P ? ablk : 0u));
-            ra[j] = bload16(ro, (uint32_t)(a_r[j] * a.HD + lfl[j] + 8 * a_c4[j]) * 2u);
-            advance(j);
+            // projection and feature offset of the half (scalar)
+            const int f = s * KC + 32 * a_hf[j];
+            const int p = (f >= a.HD) + (f >= 2 * a.HD) + (f >= 3 * a.HD);
+            const bool in = f < F && a_hf[j] < 2;
+            const char *base = uniform_ptr((const char *)dout_ptr(a, in ? p : 0) + aoff);
+            const rsrc_t ro = make_buf(base, __builtin_amdgcn_readfirstlane(in ? ablk : 0u));
+            ra[j] = bload16(ro, (uint32_t)(a_r[j] * a.HD + (f - p * a.HD) + 8 * a_c4[j]) * 2u);
         }
 #pragma unroll
         for (int j = 0; j < NWL; ++j) {  // weight rows s*KC .. (rows past F read as zeros)
             const int idx = tid + j * NT;
-            const int rr = idx / (CW / 8), c8 = idx % (CW / 8);
-            rw[j] = bload16(rW, (uint32_t)((s * KC + rr) * C + c0 + c8 * 8) * 2u);
+            const int rr = idx / (C / 8), c8 = idx % (C / 8);
+            rw[j] = bload16(rW, (uint32_t)((s * KC + rr) * C + c8 * 8) * 2u);
         }
     };
     auto store_stage = [&](int buf, const u32x4 (&ra)[NA], const u32x4 (&rw)[NWL]) {
-        uint16_t *al = lds + buf * (LW + LA) + LW;
-        uint16_t *wl = lds + buf * (LW + LA);
+        uint16_t *wl = st + buf * (G::LW + G::LA);
+        uint16_t *al = wl + G::LW;
 #pragma unroll
         for (int j = 0; j < NA; ++j)
-            *(u32x4 *)&al[a_r[j] * ASTR + 32 * a_hf[j] + 8 * a_c4[j]] = ra[j];
+            if (a_hf[j] < 2) *(u32x4 *)&al[a_r[j] * KC + 8 * ((4 * a_hf[j] + a_c4[j]) ^ akey(a_r[j]))] = ra[j];
 #pragma unroll
         for (int j = 0; j < NWL; ++j) {
             const int idx = tid + j * NT;
-            const int rr = idx / (CW / 8), c8 = idx % (CW / 8);
+            const int rr = idx / (C / 8), c8 = idx % (C / 8);
             *(u32x4 *)&wl[rr * WSTR + c8 * 8] = rw[j];
         }
     };
 
-    f32x16 acc[TPW];
+    f32x16 acc[MT][MC];
 #pragma unroll
-    for (int j = 0; j < TPW; ++j) acc[j] = zero16();
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < MC; ++j) acc[i][j] = zero16();
     u32x4 ra[NR][NA], rw[NR][NWL];
 #pragma unroll
     for (int u = 0; u < NR; ++u) load_stage(u, ra[u], rw[u]);
@@ -200,16 +220,24 @@ __global__ __launch_bounds__(DyCfg<CW>::NT) void dy_kernel(PjBwdArgs a, void *__
 #pragma unroll
         for (int u = 0; u < NR; ++u) {
             const int s = s0 + u;
-            const uint16_t *wl = lds + (u & 1) * (LW + LA);
-            const uint16_t *al = wl + LW;
+            const uint16_t *wl = st + (u & 1) * (G::LW + G::LA);
+            const uint16_t *al = wl + G::LW;
             if (s < NS) {
 #pragma unroll
                 for (int t = 0; t < 2; ++t) {
-                    const Tr<bf16_t>::K32 af = load_k32<bf16_t>(&al[(tb * 32 + n) * ASTR + 32 * t], h);
+                    Tr<bf16_t>::K32 af[MT];
 #pragma unroll
-                    for (int j = 0; j < TPW; ++j) {
-                        const Tr<bf16_t>::K32 bf = load_k32_tr(&wl[(cg + CG * j) * 32], WSTR, 32 * t, 32, lane);
-                        Tr<bf16_t>::mma_k32(acc[j], af, bf);
+                    for (int i = 0; i < MT; ++i) {
+                        const int r = (wt * MT + i) * 32 + n;
+#pragma unroll
+                        for (int q = 0; q < 2; ++q)  // chunks 4t + h and 4t + 2 + h of the row
+                            af[i].v[q] = *(const bf16x8 *)&al[r * KC + 8 * ((4 * t + 2 * q + h) ^ akey(r))];
+                    }
+#pragma unroll
+                    for (int j = 0; j < MC; ++j) {
+                        const Tr<bf16_t>::K32 bf = load_k32_tr(&wl[(wc * MC + j) * 32], WSTR, 32 * t, 32, lane);
+#pragma unroll
+                        for (int i = 0; i < MT; ++i) Tr<bf16_t>::mma_k32(acc[i][j], af[i], bf);
                     }
                 }
             }
@@ -222,25 +250,121 @@ __global__ __launch_bounds__(DyCfg<CW>::NT) void dy_kernel(PjBwdArgs a, void *__
         }
     }
 
-    // epilogue: D[token rho(i,h)][channel ct*32 + sig(n)] -> bf16 -> token rows
-    const rsrc_t rd = make_buf((char *)dy + row0 * C * 2, (uint32_t)nrows * C * 2);
-    uint16_t *st = lds + wave * 32 * OSTR;
+    if constexpr (!LN) {
+        // dY is the result: each wave's tiles as bf16 through an LDS tile of its
+        // own (16-byte stores; the stages' last reads are behind the barrier above)
+        constexpr int TSTR = 40;
+        uint16_t *const tl = st + wave * 32 * TSTR;
+        const rsrc_t ro = make_buf((char *)a.dx + row0 * C * 2, (uint32_t)nrows * C * 2u);
 #pragma unroll
-    for (int j = 0; j < TPW; ++j) {
-        const int ct = cg + CG * j;
+        for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int t = 8 * (i / 4) + 4 * h + (i % 4);
-            st[t * OSTR + sig(n)] = __builtin_bit_cast(uint16_t, (__bf16)acc[j][i]);
+            for (int j = 0; j < MC; ++j) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) tl[(8 * (e / 4) + 4 * h + (e % 4)) * TSTR + sig(n)] = f2bf(acc[i][j][e]);
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const int t = q * 16 + (lane >> 2), c4 = lane & 3;
+                    const u32x4 v = *(const u32x4 *)&tl[t * TSTR + c4 * 8];
+                    bstore16(v, ro, (uint32_t)(((wt * MT + i) * 32 + t) * C + (wc * MC + j) * 32 + c4 * 8) * 2u);
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+        return;
+    }
+    // ---- epilogue: D[token rho(i,h)][channel ct*32 + sig(n)] as fp32 rows in
+    // LDS (the stages' last reads are behind the barrier above), then whole
+    // rows: LPR lanes per row, 8 channels a lane, RPW rows per wave and pass
+    constexpr int LPR = C / 8, RPW = 64 / LPR, NP = TM / (8 * RPW);
+    float *const ot = (float *)lds;
+    const int li = lane % LPR, rs = lane / LPR;
+    const rsrc_t rx = make_buf((const char *)a.x + row0 * C * 2, (uint32_t)nrows * C * 2u);
+    u32x4 xv[NP];
+    float mv[NP], rv[NP];
+    {
+        const rsrc_t rm = make_buf(a.mean + row0, (uint32_t)nrows * 4u), rr = make_buf(a.rstd + row0, (uint32_t)nrows * 4u);
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const int r = (p * 8 + wave) * RPW + rs;
+            xv[p] = bload16(rx, (uint32_t)(r * C + 8 * li) * 2u);
+            mv[p] = __uint_as_float(bload4(rm, (uint32_t)r * 4u));
+            rv[p] = __uint_as_float(bload4(rr, (uint32_t)r * 4u));
         }
-        __builtin_amdgcn_wave_barrier();
+    }
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < MC; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int t = (wt * MT + i) * 32 + 8 * (e / 4) + 4 * h + (e % 4);
+                ot[t * G::OSTR + (wc * MC + j) * 32 + sig(n)] = acc[i][j][e];
+            }
+    float wv[8], pw[8], pb[8];
+    {
+        const rsrc_t rlw = make_buf(a.lnw, C * 4);
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-            const int t = q * 16 + (lane >> 2), c4 = lane & 3;
-            const u32x4 v = *(const u32x4 *)&st[t * OSTR + c4 * 8];
-            bstore16(v, rd, (uint32_t)((tb * 32 + t) * C + c0 + ct * 32 + c4 * 8) * 2u);
+            const f32x4 w4 = __builtin_bit_cast(f32x4, bload16(rlw, (uint32_t)(8 * li + 4 * q) * 4u));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) wv[4 * q + e] = w4[e];
         }
-        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int e = 0; e < 8; ++e) pw[e] = pb[e] = 0.0f;
+    }
+    __syncthreads();
+    const rsrc_t rd = make_buf((char *)a.dx + row0 * C * 2, (uint32_t)nrows * C * 2u);
+    constexpr float inv_c = 1.0f / (float)C;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        const int r = (p * 8 + wave) * RPW + rs;
+        bf16x8 o;
+        {
+            const f32x4 d0 = *(const f32x4 *)&ot[r * G::OSTR + 8 * li], d1 = *(const f32x4 *)&ot[r * G::OSTR + 8 * li + 4];
+            const float dy[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
+            const uint32_t xw[4] = {xv[p].x, xv[p].y, xv[p].z, xv[p].w};
+            float xh[8], g[8], sg = 0.0f, sgx = 0.0f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float x = __builtin_bit_cast(float, (e & 1) ? (xw[e / 2] & 0xffff0000u) : (xw[e / 2] << 16));
+                xh[e] = (x - mv[p]) * rv[p];
+                g[e] = dy[e] * wv[e];
+                sg += g[e];
+                sgx = __builtin_fmaf(g[e], xh[e], sgx);
+                pw[e] = __builtin_fmaf(dy[e], xh[e], pw[e]);
+                pb[e] += dy[e];
+            }
+            const float ma = row_sum<LPR>(sg) * inv_c, mc = row_sum<LPR>(sgx) * inv_c;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[e] = (__bf16)(rv[p] * (g[e] - ma - xh[e] * mc));
+        }
+        bstore16(__builtin_bit_cast(u32x4, o), rd, (uint32_t)(r * C + 8 * li) * 2u);
+    }
+    {
+        // column sums: the row slots of a wave, then the waves in order
+        float *const red = ot + TM * G::OSTR;
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+#pragma unroll
+            for (int m = LPR; m < 64; m <<= 1) {
+                pw[e] += __shfl_xor(pw[e], m, 64);
+                pb[e] += __shfl_xor(pb[e], m, 64);
+            }
+        if (rs == 0) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                red[wave * 2 * C + 8 * li + e] = pw[e];
+                red[wave * 2 * C + C + 8 * li + e] = pb[e];
+            }
+        }
+        __syncthreads();
+        if (tid < 2 * C) {
+            float t = red[tid];
+#pragma unroll
+            for (int k = 1; k < 8; ++k) t += red[k * 2 * C + tid];
+            part_ln[(int64_t)blockIdx.x * 2 * C + tid] = t;
+        }
     }
 }
 
@@ -414,51 +538,85 @@ __global__ __launch_bounds__((DwCfg<C, FB>::NT)) void dw_kernel(PjBwdArgs a, int
     }
 }
 
-// out[x] = sum_k part[k][x]: a 256-thread block takes 256 / KS groups of
-// four columns and splits k into KS interleaved slices (thread slice ks sums
-// k = ks, ks + KS, ... in order); the KS slice sums are then added in slice
-// order, so the result does not depend on timing.  Blocks past the first
-// array's columns reduce the second array.
+// Sums over the partial rows of up to three arrays in one launch:
+//   dW [n_part][width], dbias [n_part][width2]: a 256-thread block takes 256 / KS
+//   groups of four columns and splits the rows into KS interleaved slices (thread
+//   slice ks sums k = ks, ks + KS, ... in order); the slice sums are then added
+//   in slice order, so the result does not depend on timing;
+//   dln_w | dln_b [n_ln][2C] likewise with 64 slices of four groups (many
+//   rows, few columns).
+struct ColsumArgs {
+    const float *part, *part2, *part_ln;
+    float *out, *out2, *dlnw, *dlnb;
+    int64_t width, width2, n_part, n_ln;
+    int C;
+};
+
 template <int KS>
-__global__ __launch_bounds__(256) void colsum_kernel(const float *__restrict__ part, int64_t width,
-                                                    float *__restrict__ out, const float *__restrict__ part2,
-                                                    int64_t width2, float *__restrict__ out2, int64_t n_part) {
-    constexpr int QB = 256 / KS;              // four-column groups per block
-    __shared__ f32x4 red[KS > 1 ? KS : 1][QB];
-    const int ks = threadIdx.x / QB, qb = threadIdx.x % QB;
-    int64_t blk = blockIdx.x;
-    const int64_t nb1 = (width / 4 + QB - 1) / QB;
-    if (blk >= nb1) {
-        blk -= nb1;
-        part = part2;
-        width = width2;
-        out = out2;
-    }
-    const int64_t x4 = (blk * QB + qb) * 4;
-    const bool ok = x4 < width;
-    const rsrc_t rp = make_buf(part, (uint32_t)(n_part * width * 4));
+__device__ __forceinline__ f32x4 slice_sum(const float *part, int64_t width, int64_t n_part, int64_t x4, int ks,
+                                           f32x4 *red, int qb, int QB) {
+    if (x4 >= width) n_part = 0;
+    const float *p = part + x4;
     f32x4 s = {0.f, 0.f, 0.f, 0.f};
     int64_t k = ks;
     for (; k + 3 * KS < n_part; k += 4 * KS) {
         f32x4 v[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            v[u] = __builtin_bit_cast(f32x4, bload16(rp, ok ? (uint32_t)((k + u * KS) * width + x4) * 4u : kOOB));
+        for (int u = 0; u < 4; ++u) v[u] = *(const f32x4 *)(p + (k + u * KS) * width);
 #pragma unroll
         for (int u = 0; u < 4; ++u) s += v[u];
     }
-    for (; k < n_part; k += KS) s += __builtin_bit_cast(f32x4, bload16(rp, ok ? (uint32_t)(k * width + x4) * 4u : kOOB));
+    for (; k < n_part; k += KS) s += *(const f32x4 *)(p + k * width);
     if constexpr (KS > 1) {
-        red[ks][qb] = s;
+        red[ks * QB + qb] = s;
         __syncthreads();
-        if (ks != 0) return;
-        s = red[0][qb];
-#pragma unroll
-        for (int j = 1; j < KS; ++j) s += red[j][qb];
+        s = red[qb];
+#pragma unroll 4
+        for (int j = 1; j < KS; ++j) s += red[j * QB + qb];
     }
-    if (!ok) return;
-    const rsrc_t ro = make_buf(out, (uint32_t)(width * 4));
-    bstore16(__builtin_bit_cast(u32x4, s), ro, (uint32_t)x4 * 4u);
+    return s;
+}
+
+template <int KS>
+__global__ __launch_bounds__(256) void colsum_kernel(ColsumArgs c) {
+    constexpr int QB = 256 / KS;              // four-column groups per block
+    constexpr int KL = 64, QL = 256 / KL;
+    __shared__ f32x4 red[256];
+    int64_t blk = blockIdx.x;
+    const int64_t nb1 = (c.width / 4 + QB - 1) / QB, nb2 = (c.width2 / 4 + QB - 1) / QB;
+    if (blk < nb1 + nb2) {
+        const bool second = blk >= nb1;
+        if (second) blk -= nb1;
+        const int ks = threadIdx.x / QB, qb = threadIdx.x % QB;
+        const int64_t width = second ? c.width2 : c.width, x4 = (blk * QB + qb) * 4;
+        const f32x4 s = slice_sum<KS>(second ? c.part2 : c.part, width, c.n_part, x4, ks, red, qb, QB);
+        if (ks != 0 || x4 >= width) return;
+        bstore16(__builtin_bit_cast(u32x4, s), make_buf(second ? c.out2 : c.out, (uint32_t)(width * 4)),
+                 (uint32_t)x4 * 4u);
+        return;
+    }
+    blk -= nb1 + nb2;
+    const int ks = threadIdx.x / QL, qb = threadIdx.x % QL;
+    const int64_t x4 = (blk * QL + qb) * 4;
+    const f32x4 s = slice_sum<KL>(c.part_ln, 2 * c.C, c.n_ln, x4, ks, red, qb, QL);
+    if (ks != 0 || x4 >= 2 * c.C) return;
+    const bool hi = x4 >= c.C;
+    bstore16(__builtin_bit_cast(u32x4, s), make_buf(hi ? c.dlnb : c.dlnw, (uint32_t)c.C * 4u),
+             (uint32_t)(hi ? x4 - c.C : x4) * 4u);
+}
+
+template <int C, int TM>
+hipError_t launch_dy_t(const PjBwdArgs &a, float *part_ln, hipStream_t s) {
+    const unsigned nt = (unsigned)((a.R + TM - 1) / TM);
+    // one or two stages (a narrow plain layer): a ring of two, the rest would
+    // only load zeros
+    if (a.lnw)
+        hipLaunchKernelGGL((dy_kernel<C, TM, true, 4>), dim3(nt), dim3(512), 0, s, a, part_ln);
+    else if (a.P * a.HD > 128)
+        hipLaunchKernelGGL((dy_kernel<C, TM, false, 4>), dim3(nt), dim3(512), 0, s, a, part_ln);
+    else
+        hipLaunchKernelGGL((dy_kernel<C, TM, false, 2>), dim3(nt), dim3(512), 0, s, a, part_ln);
+    return hipGetLastError();
 }
 
 template <int C, int FB>
@@ -471,28 +629,15 @@ hipError_t launch_c(const PjBwdArgs &a, void *ws, const PjBwdPlan &plan, hipStre
     char *w = (char *)ws;
     // without a LayerNorm (a plain linear layer) dY is the input gradient itself
     const bool ln = a.lnw != nullptr;
-    void *dy = ln ? w + plan.off_dy : a.dx;
-    const int64_t nt = (a.R + 127) / 128;
-    // split the channels when the token blocks alone leave CUs idle
-    int ncs = 1;
-    while (ncs < C / 64 && nt * ncs < 256) ncs *= 2;
-    if (C >= 256 && ncs == 4) {
-        hipLaunchKernelGGL((dy_kernel<C, C / 4 >= 64 ? C / 4 : 64>), dim3((unsigned)nt, 4), dim3(DyCfg<64>::NT), 0, s,
-                           a, dy);
-    } else if (C >= 128 && ncs == 2) {
-        hipLaunchKernelGGL((dy_kernel<C, C / 2 >= 64 ? C / 2 : 64>), dim3((unsigned)nt, 2),
-                           dim3(DyCfg<(C / 2 >= 64 ? C / 2 : 64)>::NT), 0, s, a, dy);
+    float *pl = (float *)(w + plan.off_ln);
+    const int tm = dy_block_tokens(a.R, C);
+    hipError_t e;
+    if constexpr (C == 256) {
+        e = tm == 32 ? launch_dy_t<C, 32>(a, pl, s) : tm == 64 ? launch_dy_t<C, 64>(a, pl, s) : launch_dy_t<C, 128>(a, pl, s);
     } else {
-        hipLaunchKernelGGL((dy_kernel<C, C>), dim3((unsigned)nt), dim3(DyCfg<C>::NT), 0, s, a, dy);
+        e = launch_dy_t<C, C == 128 ? 64 : 128>(a, pl, s);
     }
-    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (ln) {  // LayerNorm backward of dY (bf16) -> dx, dln_w, dln_b
-        LnProblem lp{1, C, a.R, 0.0f};
-        LnBwdPtrs lx{a.x, a.lnw, a.mean, a.rstd, dy, a.dx, a.dlnw, a.dlnb};
-        e = launch_ln_bwd(lp, lx, w + plan.off_ln, s);
-        if (e != hipSuccess) return e;
-    }
     const int F = a.P * a.HD;
     float *pw = (float *)(w + plan.off_dw);
     float *pb = a.dbias ? (float *)(w + plan.off_db) : nullptr;
@@ -509,21 +654,19 @@ hipError_t launch_c(const PjBwdArgs &a, void *ws, const PjBwdPlan &plan, hipStre
     }
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // dW and dbias partial sums in one launch (dbias part empty without a
-    // bias); the chunk range is split over more threads when there are few
+    // dW, dbias and dln partial sums in one launch (the dbias part empty without
+    // a bias, the dln part without a LayerNorm); the chunk range is split over more threads when there are few
     // columns, so that the launch still has about 256 blocks
-    const int64_t wdw = (int64_t)F * C, wdb = a.dbias ? F : 0;
-    const int64_t q = wdw / 4;
-    if (q >= 65536) {
-        hipLaunchKernelGGL((colsum_kernel<1>), dim3((unsigned)((q + 255) / 256 + (wdb / 4 + 255) / 256)), dim3(256), 0,
-                           s, pw, wdw, a.dW, pb, wdb, a.dbias, plan.n_chunks);
-    } else if (q >= 16384) {
-        hipLaunchKernelGGL((colsum_kernel<4>), dim3((unsigned)((q + 63) / 64 + (wdb / 4 + 63) / 64)), dim3(256), 0, s,
-                           pw, wdw, a.dW, pb, wdb, a.dbias, plan.n_chunks);
-    } else {
-        hipLaunchKernelGGL((colsum_kernel<16>), dim3((unsigned)((q + 15) / 16 + (wdb / 4 + 15) / 16)), dim3(256), 0, s,
-                           pw, wdw, a.dW, pb, wdb, a.dbias, plan.n_chunks);
-    }
+    const int64_t q = (int64_t)F * C / 4;
+    ColsumArgs c{pw, pb, pl, a.dW, a.dbias, a.dlnw, a.dlnb, (int64_t)F * C, a.dbias ? F : 0, plan.n_chunks,
+                 ln ? (a.R + tm - 1) / tm : 0, C};
+    const unsigned nln = ln ? (unsigned)((2 * C / 4 + 3) / 4) : 0u;
+    auto blocks = [&](int qb) {
+        return dim3((unsigned)((q + qb - 1) / qb + (c.width2 / 4 + qb - 1) / qb) + nln);
+    };
+    if (q >= 65536) hipLaunchKernelGGL((colsum_kernel<1>), blocks(256), dim3(256), 0, s, c);
+    else if (q >= 16384) hipLaunchKernelGGL((colsum_kernel<4>), blocks(64), dim3(256), 0, s, c);
+    else hipLaunchKernelGGL((colsum_kernel<16>), blocks(16), dim3(256), 0, s, c);
     return hipGetLastError();
 }
 
@@ -550,12 +693,10 @@ PjBwdPlan plan_proj_bwd(int64_t R, int C, int HD, int P, bool ln) {
     int64_t subs = (nsub + nch - 1) / nch;
     pl.chunk_tokens = subs * 32;
     pl.n_chunks = R > 0 ? (R + pl.chunk_tokens - 1) / pl.chunk_tokens : 1;
-    LnProblem lp{1, C, R, 0.0f};
     size_t off = 0;
-    pl.off_dy = off;
-    if (ln) off += align256((size_t)R * C * 2);
+    const int tm = dy_block_tokens(R, C);
     pl.off_ln = off;
-    if (ln) off += align256(ln_bwd_workspace(lp));
+    if (ln) off += align256((size_t)((R + tm - 1) / tm) * 2 * C * 4);
     pl.off_dw = off;
     off += align256((size_t)pl.n_chunks * F * C * 4);
     pl.off_db = off;
