@@ -192,7 +192,7 @@ struct PbBwdArgs {
 };
 
 bool pair_bias_bwd_supported(int C, int H);
-int64_t pair_bias_bwd_workgroups(int64_t B, int Li, int Lj, int C);
+int64_t pair_bias_bwd_workgroups(int64_t B, int Li, int Lj, int C, int H);
 size_t pair_bias_bwd_workspace(int64_t B, int Li, int Lj, int C, int H);
 hipError_t launch_pair_bias_bwd(const PbBwdArgs &a, void *ws, hipStream_t s);
 
