@@ -150,16 +150,19 @@ __device__ __forceinline__ void bias_block_transpose(uint16_t *tile, const BiasR
 // NKT / KG waves (each stages all of the unit's queries; the first writes
 // dA, dG and Dsum), so that a call with few (row, head) units still fills
 // the chip.  Staging then runs in KG passes of the full workgroup's batch.
-template <typename T, int D, int NKT, bool BV, int KG>
-__global__ void __launch_bounds__(NKT / KG * 64) kv_kernel(KvArgs a) {
+// QG: waves per key tile.  Such a call has one wave per SIMD and is bound by
+// the latency of its serial chain of query tiles, so two waves take every
+// other query tile of one key tile and add their sums in LDS at the end.
+template <typename T, int D, int NKT, bool BV, int KG, int QG>
+__global__ void __launch_bounds__(NKT / KG * QG * 64) kv_kernel(KvArgs a) {
     using E = typename Tr<T>::elem;
     using K32 = typename Tr<T>::K32;
     constexpr int ES = sizeof(E);
     constexpr int VEC = Tr<T>::VEC;
     constexpr int CPT = D / VEC;     // 16-byte chunks per token
     constexpr int LP = NKT * 32;
-    constexpr int NW = NKT / KG;     // waves (key tiles) per workgroup
-    constexpr int NT = NW * 64;
+    constexpr int NW = NKT / KG;     // key tiles per workgroup
+    constexpr int NT = NW * QG * 64;
     constexpr int RSTR = D + VEC;    // row-major LDS stride
     constexpr int TSTR = LP + VEC;   // transposed LDS stride
     constexpr int NST = (LP * CPT + NKT * 64 - 1) / (NKT * 64);  // staged 16-byte chunks per thread and pass
@@ -182,7 +185,8 @@ __global__ void __launch_bounds__(NKT / KG * 64) kv_kernel(KvArgs a) {
     __shared__ __attribute__((aligned(16))) E dat_lds[kTr ? 8 : DO * TSTR];
     __shared__ __attribute__((aligned(16))) float lse2_lds[LP];
     __shared__ __attribute__((aligned(16))) float dsum_lds[LP];
-    __shared__ __attribute__((aligned(16))) uint16_t bt_lds[kBD ? NW * 32 * 32 : 8];
+    __shared__ __attribute__((aligned(16))) uint16_t bt_lds[kBD ? NW * QG * 32 * 32 : 8];
+    __shared__ __attribute__((aligned(16))) float sum_lds[QG > 1 ? NW * 2 * 16 * 64 : 1];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int h2 = lane >> 5, n = lane & 31;
@@ -209,7 +213,9 @@ __global__ void __launch_bounds__(NKT / KG * 64) kv_kernel(KvArgs a) {
     // ---- every load of the unit goes out first, in the order of use:
     // this wave's key tile (K, V as B operands, lane = key), its mask, the
     // lse of the staged queries, the staged tokens, the first bias tile
-    const int kt = kg * NW + wave;
+    const int kw = QG == 1 ? wave : wave % NW;  // key tile within the workgroup
+    const int qg = QG == 1 ? 0 : wave / NW;     // this wave's query tiles: qg, qg + QG, ...
+    const int kt = kg * NW + kw;
     const int key = kt * 32 + n;
     const bool kin = key < L;
     const uint32_t key_off = kin ? (uint32_t)key * stok_b : kOOB;
@@ -251,7 +257,7 @@ __global__ void __launch_bounds__(NKT / KG * 64) kv_kernel(KvArgs a) {
     const uint32_t bt_e0 = (uint32_t)key * (uint32_t)L + 8u * h2;  // element of query 8*h2 in this key's row
     float bcur[16];
     BiasRaw8<!BV> braw[2];  // kBD: raw block of the next query tile
-    if constexpr (kBD) bias_block_load(rbd, L, 0, kt, lane, braw);
+    if constexpr (kBD) bias_block_load(rbd, L, qg, kt, lane, braw);
     else load_bias16<T, BV>(rbt, bt_e0, bcur);
 
     // ---- stage Q and dA (both layouts); dA, Dsum and dG come from dO, O, G
@@ -331,12 +337,13 @@ __global__ void __launch_bounds__(NKT / KG * 64) kv_kernel(KvArgs a) {
     f32x16 dv_acc = zero16(), dk_acc = zero16();
     const int nqt = (L + 31) / 32;
 #pragma unroll
-    for (int qt = 0; qt < NKT; ++qt) {
+    for (int qi = 0; qi < NKT; qi += QG) {
+        const int qt = qi + qg;
         if (qt >= nqt) break;
         // the next tile's bias goes out first (loads complete in order)
         float bnext[kBD ? 1 : 16];
-        if (qt + 1 < NKT) {
-            if constexpr (kBD) bias_block_load(rbd, L, qt + 1, kt, lane, braw);
+        if (qi + QG < NKT) {
+            if constexpr (kBD) bias_block_load(rbd, L, qt + QG, kt, lane, braw);
             else load_bias16<T, BV>(rbt, bt_e0 + 32u * (qt + 1), bnext);
         }
         // S = Q K^T (plus the masked-key term) and dP = dA V^T for 32
@@ -389,7 +396,7 @@ __global__ void __launch_bounds__(NKT / KG * 64) kv_kernel(KvArgs a) {
         }
         Tr<T>::mma_k32(dv_acc, dat, pb);
         Tr<T>::mma_k32(dk_acc, qtf, dsb);
-        if (qt + 1 < NKT) {
+        if (qi + QG < NKT) {
             if constexpr (kBD) {
                 bias_block_transpose(bt_tile, braw, rbd, L, lane, bcur);
             } else {
@@ -399,6 +406,28 @@ __global__ void __launch_bounds__(NKT / KG * 64) kv_kernel(KvArgs a) {
         }
     }
 
+    if constexpr (QG == 2) {
+        f32x4 *const sum = reinterpret_cast<f32x4 *>(sum_lds) + kw * 8 * 64 + lane;
+        if (qg == 1) {
+#pragma unroll
+            for (int g4 = 0; g4 < 4; ++g4) {
+                sum[g4 * 64] = f32x4{dk_acc[4 * g4], dk_acc[4 * g4 + 1], dk_acc[4 * g4 + 2], dk_acc[4 * g4 + 3]};
+                sum[(4 + g4) * 64] = f32x4{dv_acc[4 * g4], dv_acc[4 * g4 + 1], dv_acc[4 * g4 + 2], dv_acc[4 * g4 + 3]};
+            }
+        }
+        __syncthreads();
+        if (qg == 1) return;
+#pragma unroll
+        for (int g4 = 0; g4 < 4; ++g4) {
+            const f32x4 x = sum[g4 * 64], y = sum[(4 + g4) * 64];
+            const float xk[4] = {x.x, x.y, x.z, x.w}, xv[4] = {y.x, y.y, y.z, y.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                dk_acc[4 * g4 + e] += xk[e];
+                dv_acc[4 * g4 + e] += xv[e];
+            }
+        }
+    }
     // ---- dK and dV of this key tile are complete (lane = key, reg = channel)
     const rsrc_t rdk = tok_buf(a.dk), rdv = tok_buf(a.dv);
 #pragma unroll
@@ -782,30 +811,37 @@ inline bool bias_direct(const Problem &p) { return p.dtype == 1; }
 // output channels over two workgroups
 inline int64_t head_halves(const Problem &p) { return p.D > 32 ? p.D / 32 : 1; }
 
-template <typename T, int D, int NKT, bool BV, int KG>
+template <typename T, int D, int NKT, bool BV, int KG, int QG>
 hipError_t launch_kv(const KvArgs &ka0, hipStream_t s) {
     KvArgs ka = ka0;
     ka.n_units = ka0.n_units * KG;
-    hipLaunchKernelGGL((kv_kernel<T, D, NKT, BV, KG>), dim3(round8(ka.n_units)), dim3(NKT / KG * 64), 0, s, ka);
+    hipLaunchKernelGGL((kv_kernel<T, D, NKT, BV, KG, QG>), dim3(round8(ka.n_units)), dim3(NKT / KG * QG * 64), 0, s,
+                       ka);
     return hipGetLastError();
 }
 
 // Key groups per (row, head) of the dK/dV pass: with fewer units than two per
 // CU, each unit's key tiles are split over two workgroups, over four at 64
-// units or fewer (at 128 units two were faster than four: each group stages
-// the whole row's Q, dO, O and G).  Tile counts that do not divide so take
-// the nearest count that does.
+// units or fewer, where a key tile has two waves as well (bf16; us of the
+// pass with one wave and two: 8 rows of 256 at 8 heads 14.0 and 10.8, 4 of
+// 384 19.2 and 14.1, 8 of 512 22.5 and 18.3).  Above 64 units staging the
+// whole row's Q, dO, O and G in every group costs more than the waves give
+// (four groups of two waves against two of one, 16 rows: 256 keys 14.6 and
+// 13.3, 448 keys 42 and 24; two groups of two waves, 32 rows of 256: 22.7
+// and 19.0).  Tile counts that do not divide so take the nearest count that
+// does.
 template <typename T, int D, int NKT, bool BV>
 hipError_t launch_kv_g(const KvArgs &ka, hipStream_t s) {
     constexpr int K4 = NKT % 4 == 0 ? 4 : NKT == 6 ? 3 : NKT == 5 || NKT == 10 ? 5 : NKT == 14 ? 7 : 1;
     constexpr int K2 = NKT >= 4 && NKT % 2 == 0 ? 2 : 1;
     if constexpr (K4 > 1) {
-        if (ka.n_units <= 64) return launch_kv<T, D, NKT, BV, K4>(ka, s);
+        constexpr int QG = sizeof(typename Tr<T>::elem) == 2 ? 2 : 1;
+        if (ka.n_units <= 64) return launch_kv<T, D, NKT, BV, K4, QG>(ka, s);
     }
     if constexpr (K2 > 1) {
-        if (ka.n_units < 512) return launch_kv<T, D, NKT, BV, K2>(ka, s);
+        if (ka.n_units < 512) return launch_kv<T, D, NKT, BV, K2, 1>(ka, s);
     }
-    return launch_kv<T, D, NKT, BV, 1>(ka, s);
+    return launch_kv<T, D, NKT, BV, 1, 1>(ka, s);
 }
 
 template <typename T, int D, int NKT>

@@ -75,12 +75,14 @@ __global__ void __launch_bounds__(kRqWaves * 64) __attribute__((amdgpu_waves_per
     constexpr int NR = NW / KS;                // rows in flight
     constexpr int NMB = (NKT * 32 + 63) / 64;  // mask bytes per lane
     constexpr int TILE = kRqTile<D>;
-    constexpr int TPS = 1;                     // accumulator tiles per wave and step of the final sum
+    // accumulator tiles per wave and step of the final sum: one in the bias area,
+    // at head_dim 32 one in each K/V buffer too
+    constexpr int TPS = D == 32 ? 3 : 1;
     // key tiles per step: two where the accumulators leave the registers for
     // it, so that one tile's exponentials run beside the other's products
     constexpr int NP = NKT <= 4 && KS <= 2 ? 2 : 1;
     constexpr int XB = KS <= 2 ? 2 : 1;        // buffers of the dQ shares (two save a barrier per row)
-    constexpr int AREA = (KS * NKT > NW * TPS ? KS * NKT : NW * TPS) * 1024;
+    constexpr int AREA = (KS * NKT > NW ? KS * NKT : NW) * 1024;
     // the bias tiles during the row loop, the accumulators of the final sum after it
     __shared__ __attribute__((aligned(16))) float area[AREA];
     // two K/V tile buffers per wave, each an array of its own so that the
@@ -337,44 +339,51 @@ __global__ void __launch_bounds__(kRqWaves * 64) __attribute__((amdgpu_waves_per
     const rsrc_t rp = make_buf(a.dst + ((b * a.H + hh) * a.chunks + chunk) * (int64_t)L * a.pitch,
                                (uint32_t)L * (uint32_t)a.pitch * 4u);
     const bool vec = a.pitch % 4 == 0;
+    auto red = [&](int j) { return j == 0 ? area : reinterpret_cast<float *>(j == 1 ? kv0_lds : kv1_lds); };
+    static_assert(TPS == 1 || NW * 2 * TILE * 2 >= NW * 1024 * 4, "a K/V buffer holds a tile of every wave");
 #pragma unroll
     for (int t0 = 0; t0 < NKT; t0 += TPS) {
-        __syncthreads();  // the reads of the bias tiles, or of the previous step
+        __syncthreads();  // the reads of the bias and K/V tiles, or of the previous step
 #pragma unroll
         for (int j = 0; j < TPS; ++j) {
             if (t0 + j >= NKT) continue;
+            float *const rj = red(j);
 #pragma unroll
             for (int g4 = 0; g4 < 4; ++g4) {
                 const f32x16 &c = acc[t0 + j < NKT ? t0 + j : 0];
                 const f32x4 x = {c[4 * g4], c[4 * g4 + 1], c[4 * g4 + 2], c[4 * g4 + 3]};
-                *reinterpret_cast<f32x4 *>(&area[((wave * TPS + j) * 4 + g4) * 256 + lane * 4]) = x;
+                *reinterpret_cast<f32x4 *>(&rj[(wave * 4 + g4) * 256 + lane * 4]) = x;
             }
         }
         __syncthreads();
-        // four consecutive keys per thread and step: (key part, tile, query, 4-key group)
+        // four consecutive keys per thread and step: (tile of the step), key
+        // part, query, 4-key group
 #pragma unroll
-        for (int j = 0; j < (KS * TPS * 256 + NW * 64 - 1) / (NW * 64); ++j) {
-            const int idx = tid + j * NW * 64;
-            if (idx >= KS * TPS * 256) continue;
-            const int c = idx & 7, q = (idx >> 3) & 31, pt = idx >> 8;  // pt: key part * TPS + tile
-            const int part = pt / TPS, tt = pt % TPS;
-            // keys 4c .. 4c+3 of the tile are registers 4 g4 .. of lane half hs
-            const int g4 = 2 * (c >> 2) + (c & 1), hs = (c >> 1) & 1;
-            f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (int j = 0; j < TPS; ++j) {
+            if (t0 + j >= NKT) continue;
+            const float *const rj = red(j);
 #pragma unroll
-            for (int w = 0; w < NR; ++w)
-                sum += *reinterpret_cast<const f32x4 *>(
-                    &area[(((w * KS + part) * TPS + tt) * 4 + g4) * 256 + (hs * 32 + q) * 4]);
-            const int key = (part * NKT + t0 + tt) * 32 + 4 * c, qq = qt * 32 + q;
-            const bool ok = t0 + tt < NKT && qq < L && key < L;
-            const uint32_t off = ok ? (uint32_t)(qq * a.pitch + key) * 4u : kOOB;
-            if (vec) {
-                bstore16(__builtin_bit_cast(u32x4, sum), rp, off);
-            } else {
-                const float v[4] = {sum.x, sum.y, sum.z, sum.w};
+            for (int i = 0; i < (KS * 256 + NW * 64 - 1) / (NW * 64); ++i) {
+                const int idx = tid + i * NW * 64;
+                if (idx >= KS * 256) continue;
+                const int c = idx & 7, q = (idx >> 3) & 31, part = idx >> 8;
+                // keys 4c .. 4c+3 of the tile are registers 4 g4 .. of lane half hs
+                const int g4 = 2 * (c >> 2) + (c & 1), hs = (c >> 1) & 1;
+                f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    bstore4(__builtin_bit_cast(uint32_t, v[e]), rp, ok && key + e < L ? off + 4u * e : kOOB);
+                for (int w = 0; w < NR; ++w)
+                    sum += *reinterpret_cast<const f32x4 *>(&rj[((w * KS + part) * 4 + g4) * 256 + (hs * 32 + q) * 4]);
+                const int key = (part * NKT + t0 + j) * 32 + 4 * c, qq = qt * 32 + q;
+                const bool ok = qq < L && key < L;
+                const uint32_t off = ok ? (uint32_t)(qq * a.pitch + key) * 4u : kOOB;
+                if (vec) {
+                    bstore16(__builtin_bit_cast(u32x4, sum), rp, off);
+                } else {
+                    const float v[4] = {sum.x, sum.y, sum.z, sum.w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        bstore4(__builtin_bit_cast(uint32_t, v[e]), rp, ok && key + e < L ? off + 4u * e : kOOB);
+                }
             }
         }
     }
