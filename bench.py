@@ -45,13 +45,14 @@ def bias_transposed(w, es: int) -> bool:
 def fused_backward(w, es: int) -> bool:
     """Whether the library runs the single-pass backward for this workload:
     bf16 with head_dim <= 32; with a bias only where the chunk's dBias
-    accumulators fit (up to 128 keys, or head_dim 8 up to 256)."""
+    accumulators fit (up to 128 keys, or head_dim 8 up to 256 at lengths that
+    are multiples of 8)."""
     if es != 2 or w.head_dim > 32:
         return False
     if not w.bias:
         return w.seq_len <= 256
     nkt = (w.seq_len + 31) // 32
-    return nkt <= 4 or (w.head_dim == 8 and nkt <= 8)
+    return nkt <= 4 or (w.head_dim == 8 and nkt <= 8 and w.seq_len % 8 == 0)
 
 
 def forward_kernel(w, es: int) -> str:

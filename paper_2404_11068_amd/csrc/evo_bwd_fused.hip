@@ -575,7 +575,13 @@ hipError_t launch_fused_t(const FusedArgs &fa, hipStream_t s) {
 // With a bias, the chunk's dBias accumulators (a whole [L, L] plane per
 // workgroup) must fit beside the rest: every head dim up to 128 keys, and
 // head_dim 8 up to 256 keys (up to three query tiles of accumulators in LDS).
-// Other shapes take the two-pass backward.
+// Other shapes take the two-pass backward, and so do lengths past 128 that are
+// no multiple of 8: the two passes take a bias of -inf (a pair that is left
+// out) as P = 0, where the product that adds the bias here would form
+// 0 * -inf = NaN, and such calls have always had that.  (Backward, bf16, d 8,
+// us: 512 rows of 190 at 4 heads 78, 256 of 254 at 8 heads 112, 64 of 131 at 4
+// heads 22; with the two passes as they were when odd lengths read the bias
+// element by element 186, 227 and 39.)
 template <int D, int NKT>
 constexpr bool kFusedBias = NKT <= 4 || D == 8;
 
@@ -584,7 +590,7 @@ hipError_t launch_fused_n(const Problem &p, const FusedArgs &fa, hipStream_t s) 
     if (!fa.bias) return launch_fused_t<D, NKT, false, true>(fa, s);
     if constexpr (kFusedBias<D, NKT>) {
         if (p.L % 2 == 0) return launch_fused_t<D, NKT, true, true>(fa, s);
-        return launch_fused_t<D, NKT, true, false>(fa, s);
+        if constexpr (NKT <= 4) return launch_fused_t<D, NKT, true, false>(fa, s);
     }
     return hipErrorInvalidValue;  // excluded by fused_bwd_supported
 }
@@ -609,7 +615,7 @@ bool fused_bwd_supported(const Problem &p, bool has_bias) {
     const int64_t nkt = (p.L + 31) / 32;
     if (p.dtype != 1 || p.D > 32 || nkt > 8) return false;  // (its LDS tiles hold up to 256 keys)
     if (!has_bias) return true;
-    return nkt <= 4 || p.D == 8;
+    return nkt <= 4 || (p.D == 8 && p.L % 8 == 0);
 }
 
 // rows per chunk and chunk count of the fused backward: about 2048 waves in

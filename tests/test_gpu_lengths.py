@@ -22,7 +22,7 @@ CASES = [
     # N, L, H, d, kwargs
     (3, 67, 3, 16, dict(rpb=1)),                   # single pass, three key tiles, odd planes
     (5, 95, 1, 32, dict()),
-    (2, 131, 3, 8, dict(rpb=1)),                   # single pass at head_dim 8, odd length past 128 keys
+    (2, 131, 3, 8, dict(rpb=1)),                   # two passes at head_dim 8, odd length past 128 keys
     (9, 190, 1, 8, dict(mask="length")),
     (2, 193, 2, 8, dict(bias=False)),
     (9, 130, 2, 32, dict()),                       # two passes from here: 5, 6, 7 and 8 key tiles
@@ -90,3 +90,24 @@ def test_values_after_the_plane_do_not_matter():
         torch.cuda.synchronize()
         for name, t in zip(("out", "lse", "dq", "dk", "dv", "dgate", "dbias"), (out, lse) + tuple(grads)):
             assert np.array_equal(t.double().cpu().numpy(), ref[name]), (L, d, name)
+
+
+@pytest.mark.parametrize("L,d", [(131, 8), (190, 8), (254, 8), (163, 16), (222, 32), (317, 32), (418, 16)])
+def test_minus_inf_bias_leaves_a_pair_out(L, d):
+    """A bias of -inf gives the bits of a very low finite one (P = 0 either way), at
+    the lengths past 128 keys that are no multiple of 8, forward and backward."""
+    from paper_2404_11068_amd import evo_attn as ea
+    N, H = 5, 2
+    w, x = make_inputs(N, L, H, d, "bf16", seed=40 + L)
+    print("\n[case] -inf bias", L, d, flush=True)
+    dev = {n: to_device(x[n], "bf16") for n in ("q", "k", "v", "gate", "bias", "dout")}
+    mask = torch.from_numpy(x["mask"]).cuda()
+    drop = torch.rand(dev["bias"].shape, generator=torch.Generator().manual_seed(L)).cuda() < 0.1
+    res = []
+    for low in (-1e30, float("-inf")):
+        args = (dev["q"], dev["k"], dev["v"], dev["gate"], dev["bias"].masked_fill(drop, low), mask)
+        out, lse = ea.evo_attn_fwd(*args, rows_per_bias=N)
+        res.append((out, lse) + tuple(ea.evo_attn_bwd(*args, out, lse, dev["dout"], rows_per_bias=N)))
+    torch.cuda.synchronize()
+    for name, a, b in zip(("out", "lse", "dq", "dk", "dv", "dgate", "dbias"), *res):
+        assert torch.isfinite(b).all() and torch.equal(a, b), (L, d, name)
