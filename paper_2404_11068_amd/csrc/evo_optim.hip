@@ -69,11 +69,7 @@ __device__ __forceinline__ void adam_elem(const AdamArgs &h, float gs, float &p,
 __global__ __launch_bounds__(kMtThreads) void adam_swa_kernel(AdamArgs h, const evo_mt_tensor *__restrict__ tensors,
                                                              int32_t n_tensors, const evo_mt_chunk *__restrict__ chunks,
                                                              const float *__restrict__ grad_scale) {
-    // Last chunk first: the norm pass before it read the gradients first to
-    // last, so the newest of them are still in the memory-side cache (5019
-    // tensors, 94.4M parameters, clipping included: 644.4 -> 638.2 us, 5.27 ->
-    // 5.33 TB/s; any other order would read all of them from HBM again).
-    const evo_mt_chunk c = chunks[gridDim.x - 1 - blockIdx.x];
+    const evo_mt_chunk c = chunks[blockIdx.x];
     evo_mt_tensor t;
     const ChunkView cv = chunk_view(tensors, n_tensors, c, t);
     if (!cv.ok) return;
