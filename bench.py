@@ -71,6 +71,20 @@ def forward_kernel(w, es: int) -> str:
     return "fwd_rows_kernel" if g > 0 and units >= 2 * g0 else "fwd_kernel"
 
 
+def dq_kernel(w, es: int) -> str:
+    """The kernel of the two-pass backward's dQ/dBias pass: rows_qbias_kernel for
+    bf16 at head_dim <= 32 unless few rows share a bias plane (up to three; four
+    up to 256 keys with a workgroup for every CU) at lengths that are multiples of
+    8, qbias_kernel otherwise."""
+    if es != 2 or w.head_dim > 32:
+        return "qbias_kernel"
+    if not w.bias or w.seq_len % 8:
+        return "rows_qbias_kernel"
+    wgs = w.n_rows // w.rows_per_bias * w.n_heads * ((w.seq_len + 31) // 32)
+    few = w.rows_per_bias <= 3 or (w.rows_per_bias == 4 and w.seq_len <= 256 and wgs >= 256)
+    return "qbias_kernel" if few else "rows_qbias_kernel"
+
+
 def kernel_model(w, es: int, ws_bytes: int):
     """Per-launch traffic and MFMA flops of every kernel of one step, in launch
     order, as (name, algorithmic bytes, workspace bytes, flops).
@@ -114,11 +128,10 @@ def kernel_model(w, es: int, ws_bytes: int):
                T + dsum + biast, 8.0 * S * d))
     # dQ/dBias pass: reads Q K V lse bias mask, writes dQ; workspace: reads dA
     # and Dsum, writes the partial dBias planes
-    # (bf16 up to head_dim 32: rows_qbias_kernel, which writes dBias itself with one row chunk)
-    rows = es == 2 and d <= 32
-    ks.append(("rows_qbias_kernel" if rows else "qbias_kernel",
-               3 * T + lse + bias + mask + T + (dbias if rows and not parts else 0), T + dsum + parts, 6.0 * S * d))
-    if w.bias and (parts or not rows):
+    # (bf16 up to head_dim 32 writes dBias itself where a plane has one row chunk)
+    direct = es == 2 and d <= 32 and not parts
+    ks.append((dq_kernel(w, es), 3 * T + lse + bias + mask + T + (dbias if direct else 0), T + dsum + parts, 6.0 * S * d))
+    if w.bias and not direct:
         ks.append(("dbias_reduce", dbias, parts, 0.0))
     return ks
 

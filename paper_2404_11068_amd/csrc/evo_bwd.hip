@@ -19,8 +19,9 @@
 //           lane = key, registers = queries.  dK and dV finish in registers.
 //           It also does the elementwise part (dA, Dsum, dG) while staging,
 //           and leaves dA and Dsum in the workspace for the second pass.
-//   qbias   (fp32, and bf16 at head_dim 64; bf16 up to head_dim 32 runs
-//           rows_qbias_kernel in evo_bwd_qbias.hip instead)
+//   qbias   (fp32, bf16 at head_dim 64, and bf16 up to head_dim 32 where few
+//           rows share a bias plane (few_rows_per_plane); the rest of bf16 runs
+//           rows_qbias_kernel in evo_bwd_qbias.hip)
 //           one workgroup per (bias plane, head, 32-query tile, chunk of
 //           rows); wave w owns key tile w, lane = query, registers = keys.
 //           dQ is summed over the waves through LDS in a fixed order; dS is
@@ -496,7 +497,10 @@ __global__ void __launch_bounds__(NKT * 64) __attribute__((amdgpu_waves_per_eu(4
     constexpr int CPT = D / VEC;            // 16-byte chunks per token
     constexpr int LP = NKT * 32;
     constexpr int NT = NKT * 64;
-    constexpr int KSTR = D + VEC;           // row stride of K, V, Q, dA tiles in LDS (elements)
+    // bf16 rows of 32 channels use the swizzled 64-byte layout (sw32);
+    // otherwise rows are padded by one 16-byte chunk
+    constexpr bool kSw = kTr && D == 32;
+    constexpr int KSTR = kSw ? D : D + VEC;  // row stride of K, V, Q, dA tiles in LDS (elements)
     constexpr int NKV = (LP * CPT + NT - 1) / NT;  // 16-byte chunks of K (and of V) per thread
     constexpr int NQC = (32 * CPT + NT - 1) / NT;  // 16-byte chunks of the Q (and dA) tile per thread
     // output channels per workgroup: head_dim 64 runs as two units per (row
@@ -606,7 +610,7 @@ __global__ void __launch_bounds__(NKT * 64) __attribute__((amdgpu_waves_per_eu(4
             const int idx = tid + j * NT;
             if (idx < LP * CPT) {
                 const int t = idx / CPT, c = (idx % CPT) * VEC;
-                const int o = t * KSTR + c;
+                const int o = kSw ? sw32(t, idx % CPT) : t * KSTR + c;
                 *reinterpret_cast<u32x4 *>(&k_lds[o]) = kr[j];
                 *reinterpret_cast<u32x4 *>(&v_lds[o]) = vr[j];
             }
@@ -616,7 +620,7 @@ __global__ void __launch_bounds__(NKT * 64) __attribute__((amdgpu_waves_per_eu(4
             const int idx = tid + j * NT;
             if (idx < 32 * CPT) {
                 const int t = idx / CPT, c = (idx % CPT) * VEC;
-                const int o = t * KSTR + c;
+                const int o = kSw ? sw32(t, idx % CPT) : t * KSTR + c;
                 *reinterpret_cast<u32x4 *>(&q_lds[o]) = qr[j];
                 *reinterpret_cast<u32x4 *>(&da_lds[o]) = dar[j];
             }
@@ -640,10 +644,17 @@ __global__ void __launch_bounds__(NKT * 64) __attribute__((amdgpu_waves_per_eu(4
         f32x16 dq = zero16();
         if (kbits != 0) {
             ChFrag<T, D> qb, dab, ka, va;
-            qb.load(&q_lds[n * KSTR], h2);
-            dab.load(&da_lds[n * KSTR], h2);
-            ka.load(&k_lds[(kt * 32 + sig(n)) * KSTR], h2);
-            va.load(&v_lds[(kt * 32 + sig(n)) * KSTR], h2);
+            if constexpr (kSw) {
+                load_sw32(qb, q_lds, n, h2);
+                load_sw32(dab, da_lds, n, h2);
+                load_sw32(ka, k_lds, kt * 32 + sig(n), h2);
+                load_sw32(va, v_lds, kt * 32 + sig(n), h2);
+            } else {
+                qb.load(&q_lds[n * KSTR], h2);
+                dab.load(&da_lds[n * KSTR], h2);
+                ka.load(&k_lds[(kt * 32 + sig(n)) * KSTR], h2);
+                va.load(&v_lds[(kt * 32 + sig(n)) * KSTR], h2);
+            }
             const float l2 = lse2_lds[n], ds = dsum_lds[n];
             // S^T = K Q^T + sqrt(d) bias^T, dP^T = V dA^T: lane = query, reg i = key kt*32 + krow(i, h2)
             f32x16 S = bacc, dP = zero16();
@@ -674,7 +685,9 @@ __global__ void __launch_bounds__(NKT * 64) __attribute__((amdgpu_waves_per_eu(4
             }
             // dQ^T (channels x queries) = K^T dS^T over this wave's keys
             K32 kT;
-            if constexpr (kTr) {
+            if constexpr (kSw) {
+                kT = load_k32_tr_sw32(k_lds, kt * 32, lane);
+            } else if constexpr (kTr) {
                 kT = load_k32_tr(k_lds + c_off, KSTR, kt * 32, DO, lane);
             } else {
                 const int c = sig(n);
@@ -877,27 +890,52 @@ hipError_t launch_kv_d(const Problem &p, const KvArgs &ka, hipStream_t s) {
     }
 }
 
+// bf16 up to head_dim 32: the calls that qbias_kernel takes, all its waves on
+// one row.  rows_qbias_kernel gives a row to one, two or four of its eight waves
+// and has one workgroup to a CU, so with fewer rows in a plane than row slots
+// most of its waves repeat a row.  Whole backward, bf16, d 32, H 8, us with
+// rows_qbias and with qbias:
+//   rows per plane     1           2           3           4           8
+//   64 x 160 keys    87, 48      53, 37      44, 35      39, 35      35, 40
+//   64 x 256        169, 90      98, 66      74, 57      66, 56      55, 52
+//   64 x 512        517, 442    315, 310    251, 230    246, 241    201, 202
+//   8 x 160                      17, 16                  17, 18      20, 21
+// (60 rows for three to a plane.)  Four rows pay up to 256 keys where rows_qbias
+// has a workgroup for every CU.  At lengths that are no multiple of 8, where
+// qbias reads the bias and writes dBias element by element, it is level at best
+// (64 x 251, two rows: 110, 105; 64 x 500, one row: 500, 667).
+inline bool few_rows_per_plane(const Problem &p, bool has_bias) {
+    if (!has_bias || p.dtype != 1 || p.D > 32 || p.L % 8 != 0) return false;
+    if (p.rpb <= 3) return true;
+    return p.rpb == 4 && p.L <= 256 && p.N / p.rpb * p.H * ((p.L + 31) / 32) >= 256;
+}
+
 template <typename T, int D, int NKT>
 hipError_t launch_qb_v(const Problem &p, const QbArgs &qa, hipStream_t s) {
     // BV: bias rows split into whole 16-byte groups
     if (p.L % Tr<T>::VEC == 0)
         hipLaunchKernelGGL((qbias_kernel<T, D, NKT, true>), dim3(round8(qa.n_units)), dim3(NKT * 64), 0, s, qa);
+    else if constexpr (sizeof(typename Tr<T>::elem) == 2 && D <= 32)
+        return hipErrorInvalidValue;  // excluded by few_rows_per_plane
     else
         hipLaunchKernelGGL((qbias_kernel<T, D, NKT, false>), dim3(round8(qa.n_units)), dim3(NKT * 64), 0, s, qa);
     return hipGetLastError();
 }
 
-// fp32, and bf16 at head_dim 64 (bf16 up to head_dim 32: evo_bwd_qbias.hip)
 template <typename T, int D>
 hipError_t launch_qb_d(const Problem &p, const QbArgs &qa, hipStream_t s) {
     const int64_t nkt = (p.L + 31) / 32;
-    if (nkt <= 1) return launch_qb_v<T, D, 1>(p, qa, s);
-    if (nkt <= 2) return launch_qb_v<T, D, 2>(p, qa, s);
-    if (nkt <= 4) return launch_qb_v<T, D, 4>(p, qa, s);
-    if constexpr (sizeof(typename Tr<T>::elem) == 2 || D <= 32) {
-        if (nkt <= 8) return launch_qb_v<T, D, 8>(p, qa, s);
+    if constexpr (sizeof(typename Tr<T>::elem) == 2 && D <= 32) {  // (up to 128 keys: the single-pass backward)
+        return nkt <= 8 ? launch_qb_v<T, D, 8>(p, qa, s) : launch_qb_v<T, D, 16>(p, qa, s);
+    } else {
+        if (nkt <= 1) return launch_qb_v<T, D, 1>(p, qa, s);
+        if (nkt <= 2) return launch_qb_v<T, D, 2>(p, qa, s);
+        if (nkt <= 4) return launch_qb_v<T, D, 4>(p, qa, s);
+        if constexpr (sizeof(typename Tr<T>::elem) == 2 || D <= 32) {
+            if (nkt <= 8) return launch_qb_v<T, D, 8>(p, qa, s);
+        }
+        return hipErrorInvalidValue;
     }
-    return hipErrorInvalidValue;
 }
 
 // the dK/dV pass; grids are rounded up to a multiple of 8 for the XCD-aware
@@ -914,15 +952,11 @@ hipError_t launch_kv_pass(const Problem &p, const KvArgs &ka, hipStream_t s) {
 
 template <typename T>
 hipError_t launch_qb_pass(const Problem &p, const QbArgs &qa, hipStream_t s) {
-    if constexpr (sizeof(typename Tr<T>::elem) == 2) {
-        return launch_qb_d<T, 64>(p, qa, s);
-    } else {
-        switch (p.D) {
-            case 8: return launch_qb_d<T, 8>(p, qa, s);
-            case 16: return launch_qb_d<T, 16>(p, qa, s);
-            case 64: return launch_qb_d<T, 64>(p, qa, s);
-            default: return launch_qb_d<T, 32>(p, qa, s);
-        }
+    switch (p.D) {
+        case 8: return launch_qb_d<T, 8>(p, qa, s);
+        case 16: return launch_qb_d<T, 16>(p, qa, s);
+        case 64: return launch_qb_d<T, 64>(p, qa, s);
+        default: return launch_qb_d<T, 32>(p, qa, s);
     }
 }
 
@@ -959,20 +993,21 @@ hipError_t launch_bwd_t(const Problem &p, const BwdPtrs &x, void *ws, const BwdP
     e = launch_kv_pass<T>(p, ka, s);
     if (e != hipSuccess) return e;
     tr.mark(s);
-    if (rows_qbias_supported(p))
+    if (plan.key_parts > 0)
         return launch_rows_qbias(p, x, ka.da, ka.dsum, (float *)(w + plan.off_part), plan.chunks, plan.rows_per_chunk,
                               plan.key_parts, s, tr);
     QbArgs qa;
     qa.q = x.q; qa.k = x.k; qa.v = x.v; qa.bias = x.bias; qa.mask = x.mask; qa.lse = x.lse;
     qa.da = ka.da; qa.dsum = ka.dsum; qa.dq = x.dq;
-    qa.part = x.bias ? (float *)(w + plan.off_part) : nullptr;
+    const bool direct = few_rows_per_plane(p, x.bias != nullptr);  // one row chunk: the sums are dBias
+    qa.part = direct ? x.dbias : x.bias ? (float *)(w + plan.off_part) : nullptr;
     qa.L = p.L; qa.rpb = rpb; qa.srow = p.srow; qa.stok = p.stok;
     qa.chunks = plan.chunks; qa.rows_per_chunk = plan.rows_per_chunk;
     qa.H = p.H; qa.scale = scale;
     qa.n_units = plan.n_wg;
     e = launch_qb_pass<T>(p, qa, s);
     if (e == hipSuccess) tr.mark(s);
-    if (e != hipSuccess || !x.bias) return e;
+    if (e != hipSuccess || !x.bias || direct) return e;
     const int64_t pe = p.L * p.L;
     int64_t blocks = (planes * pe + 255) / 256;
     if (blocks > 8192) blocks = 8192;
@@ -1035,9 +1070,12 @@ BwdPlan plan_bwd(const Problem &p, bool has_bias, size_t cap) {
     // workgroups gain (16 rows over 8 heads: 4 chunks beat 8; one-wave
     // workgroups of 32-key rows gain from every extra chunk instead)
     int64_t chunks = 0;
-    const bool rows_qbias = rows_qbias_supported(p);
-    int key_parts = 1;
-    if (rows_qbias) {
+    const bool few_rows = few_rows_per_plane(p, has_bias);
+    const bool rows_qbias = rows_qbias_supported(p) && !few_rows;
+    int key_parts = 0;
+    if (few_rows) {
+        chunks = planes > 0 ? 1 : 0;
+    } else if (rows_qbias) {
         int64_t g = 1;
         if (planes > 0 && rpb > 0 && nqt > 0) rows_qbias_chunks(p, has_bias, &chunks, &g, &key_parts);
     } else if (planes > 0 && rpb > 0 && nqt > 0) {
@@ -1069,8 +1107,8 @@ BwdPlan plan_bwd(const Problem &p, bool has_bias, size_t cap) {
         if (has_bias && !bias_direct(p)) off = align256(off + (size_t)(planes * p.H * p.L * p.L * es));
         pl.key_parts = key_parts;
         pl.off_part = off;
-        // (bf16 with one row chunk per plane writes dBias directly)
-        if (has_bias && !rows_qbias) off = align256(off + (size_t)(planes * p.H * c * p.L * p.L) * 4);
+        // (bf16 up to head_dim 32 with one row chunk per plane writes dBias directly)
+        if (has_bias && !rows_qbias && !few_rows) off = align256(off + (size_t)(planes * p.H * c * p.L * p.L) * 4);
         if (has_bias && rows_qbias && c > 1)
             off = align256(off + (size_t)(planes * p.H * c * p.L * rows_qbias_pitch(p)) * 4);
         pl.total = off;

@@ -43,7 +43,7 @@ struct BwdPlan {
     int64_t chunks;          // row chunks per bias plane (dBias partial planes per plane and head)
     int64_t rows_per_chunk;  // rows handled by one workgroup of the dBias-producing pass
     int64_t n_wg;            // workgroups of the qbias kernel (two-pass plan)
-    int key_parts;           // waves that share a row in the rows_qbias kernel (two-pass plan, bf16, head_dim <= 32)
+    int key_parts;           // two-pass plan: waves that share a row in the rows_qbias kernel, 0 for the qbias kernel
     size_t off_da, off_dsum, off_biast, off_part, total;
 };
 

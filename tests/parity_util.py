@@ -11,6 +11,7 @@ every MFMA input and every output to bf16 (relative 2^-9 each) produces.
 from __future__ import annotations
 
 import numpy as np
+import pytest
 import torch
 
 import oracle
@@ -61,6 +62,22 @@ def oracle_run(x: dict, dtype: str, rows_per_bias: int):
     dq, dk, dv, dg, db = oracle.backward(f["q"], f["k"], f["v"], f["dout"], f["gate"], f["bias"],
                                          x["mask"], rows_per_bias)
     return dict(out=out, lse=lse, dq=dq, dk=dk, dv=dv, dgate=dg, dbias=db)
+
+
+def kernels_run(fn):
+    """The library's kernels that fn launches, in order, as "name<arguments>" (from
+    the profiler's kernel records); skips the test where it keeps none."""
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        fn()
+        torch.cuda.synchronize()
+    names = [e.name.split("::")[-1] if "<" not in e.name else e.name[:e.name.rindex("(")]
+             for e in sorted(prof.events(), key=lambda e: e.time_range.start) if "evo::" in e.name]
+    if not names:
+        pytest.skip("the profiler keeps no kernel records here")
+    return [n.replace("void ", "").replace("evo::", "").replace("(anonymous namespace)::", "").replace("bf16_t, ", "")
+            for n in names]
 
 
 def compare(got: dict, ref: dict, dtype: str, names=None, label=""):

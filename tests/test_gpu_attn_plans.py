@@ -1,0 +1,69 @@
+"""Which kernels the attention passes launch for a call, and what these give
+against the fp64 oracle (tolerances of parity_util), at sizes where the rules
+that choose them change.  The kernels' names come from the profiler; where the
+bench model mirrors a rule, the mirror is checked against them too."""
+import os
+import sys
+
+import pytest
+import torch
+
+from tests.parity_util import compare, gpu_run, kernels_run, make_inputs, oracle_run, to_device
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+sys.path.insert(0, ROOT)
+
+import bench  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def run_named(x, rpb):
+    """(results, kernel names of the forward and the backward)"""
+    names = kernels_run(lambda: gpu_run(x, "bf16", rpb))
+    return gpu_run(x, "bf16", rpb), names
+
+
+# The dQ/dBias pass where few rows share a bias plane: (N, L, H, d, rows per
+# plane, kernel).  Up to three rows qbias_kernel (8 waves up to 256 keys, 16
+# past them), which writes dBias itself; four up to 256 keys where rows_qbias
+# has a workgroup for every CU; never at lengths that are no multiple of 8.
+FEW = [
+    (3, 136, 2, 16, 1, "qbias_kernel<16, 8, true>"),
+    (6, 160, 2, 32, 3, "qbias_kernel<32, 8, true>"),
+    (4, 256, 1, 32, 2, "qbias_kernel<32, 8, true>"),
+    (4, 216, 3, 16, 2, "qbias_kernel<16, 8, true>"),
+    (3, 264, 2, 8, 3, "qbias_kernel<8, 16, true>"),
+    (2, 512, 1, 32, 1, "qbias_kernel<32, 16, true>"),
+    (4, 376, 1, 16, 2, "qbias_kernel<16, 16, true>"),
+    (104, 136, 2, 16, 4, "qbias_kernel<16, 8, true>"),   # 26 planes x 2 heads x 5 query tiles
+    (100, 136, 2, 16, 4, "rows_qbias_kernel<"),          # 25 planes: 250 workgroups
+    (4, 264, 2, 32, 4, "rows_qbias_kernel<"),
+    (5, 136, 2, 32, 5, "rows_qbias_kernel<"),
+    (3, 140, 2, 32, 1, "rows_qbias_kernel<"),
+]
+
+
+@pytest.mark.parametrize("case", FEW, ids=lambda c: "N%dL%dH%dd%drpb%d" % c[:5])
+def test_few_rows_per_bias_plane(case):
+    N, L, H, d, rpb, kernel = case
+    w, x = make_inputs(N, L, H, d, "bf16", rpb=rpb, mask="length", seed=60 + L)
+    print("\n[case]", case, flush=True)
+    got, names = run_named(x, rpb)
+    compare(got, oracle_run(x, "bf16", rpb), "bf16", label=str(case))
+    ran = [n for n in names if "qbias_kernel" in n]
+    assert len(ran) == 1 and ran[0].startswith(kernel), names
+    assert ran[0].startswith(bench.dq_kernel(w, 2) + "<")
+
+
+def test_few_rows_without_a_workspace():
+    """The no-alloc entry point gives the same bits."""
+    from paper_2404_11068_amd import evo_attn as ea
+    w, x = make_inputs(6, 200, 2, 32, "bf16", rpb=2, seed=3)
+    dev = {n: to_device(x[n], "bf16") for n in ("q", "k", "v", "gate", "bias", "dout")}
+    args = (dev["q"], dev["k"], dev["v"], dev["gate"], dev["bias"], torch.from_numpy(x["mask"]).cuda())
+    out, lse = ea.evo_attn_fwd(*args, rows_per_bias=2)
+    a = ea.evo_attn_bwd(*args, out, lse, dev["dout"], rows_per_bias=2)
+    b = ea.evo_attn_bwd_noalloc(*args, out, lse, dev["dout"], rows_per_bias=2)
+    torch.cuda.synchronize()
+    assert all(torch.equal(s, t) for s, t in zip(a, b))
