@@ -73,16 +73,28 @@ def forward_kernel(w, es: int) -> str:
 
 def dq_kernel(w, es: int) -> str:
     """The kernel of the two-pass backward's dQ/dBias pass: rows_qbias_kernel for
-    bf16 at head_dim <= 32 unless few rows share a bias plane (up to three; four
-    up to 256 keys with a workgroup for every CU) at lengths that are multiples of
-    8, qbias_kernel otherwise."""
+    bf16 at head_dim <= 32 unless qbias_kernel (one row at a time per workgroup)
+    costs no more by the library's rule, which compares rounds of workgroups and
+    partial dBias planes; qbias_kernel otherwise."""
     if es != 2 or w.head_dim > 32:
         return "qbias_kernel"
     if not w.bias or w.seq_len % 8:
         return "rows_qbias_kernel"
-    wgs = w.n_rows // w.rows_per_bias * w.n_heads * ((w.seq_len + 31) // 32)
-    few = w.rows_per_bias <= 3 or (w.rows_per_bias == 4 and w.seq_len <= 256 and wgs >= 256)
-    return "qbias_kernel" if few else "rows_qbias_kernel"
+    up = lambda a, b: -(-a // b)
+    rpb, nqt = w.rows_per_bias, up(w.seq_len, 32)
+    base = w.n_rows // rpb * w.n_heads * nqt  # workgroups per row chunk
+    wide = nqt > 8
+    k0 = (1 if nqt <= 7 else 2 if nqt <= 12 else 4) if w.head_dim == 32 else (2 if wide else 1)
+    cost, rc = min((up(base * c, 256) * (up(up(rpb, c), 8 // k) * up(nqt, k) + 6), k, c)
+                   for k in ([k0] if wide or k0 == 2 else [1, 2]) for c in range(1, min(rpb, 64) + 1))[::2]
+    rc = up(rpb, up(rpb, rc))
+    qc = max(1, min(up(4096, base * (16 if wide else 8)), rpb // 4))
+    g = up(rpb, qc)
+    qc = up(rpb, g)
+    plane_kb = w.n_rows // rpb * w.n_heads * w.seq_len ** 2 * 4 // 1000
+    parts = lambda c: c * plane_kb * 4 // 5 if c > 1 else 0
+    q = up(base * qc, 256 if wide else 512) * (g * 2500 + 3000 if wide else g * 2000 + 2000) + parts(qc)
+    return "qbias_kernel" if q <= cost * 1000 + parts(rc) else "rows_qbias_kernel"
 
 
 def kernel_model(w, es: int, ws_bytes: int):

@@ -19,9 +19,9 @@
 //           lane = key, registers = queries.  dK and dV finish in registers.
 //           It also does the elementwise part (dA, Dsum, dG) while staging,
 //           and leaves dA and Dsum in the workspace for the second pass.
-//   qbias   (fp32, bf16 at head_dim 64, and bf16 up to head_dim 32 where few
-//           rows share a bias plane (few_rows_per_plane); the rest of bf16 runs
-//           rows_qbias_kernel in evo_bwd_qbias.hip)
+//   qbias   (fp32, bf16 at head_dim 64, and bf16 up to head_dim 32 where it
+//           costs less than rows_qbias_kernel of evo_bwd_qbias.hip, which the
+//           rest of bf16 runs: plan_bwd)
 //           one workgroup per (bias plane, head, 32-query tile, chunk of
 //           rows); wave w owns key tile w, lane = query, registers = keys.
 //           dQ is summed over the waves through LDS in a fixed order; dS is
@@ -890,33 +890,13 @@ hipError_t launch_kv_d(const Problem &p, const KvArgs &ka, hipStream_t s) {
     }
 }
 
-// bf16 up to head_dim 32: the calls that qbias_kernel takes, all its waves on
-// one row.  rows_qbias_kernel gives a row to one, two or four of its eight waves
-// and has one workgroup to a CU, so with fewer rows in a plane than row slots
-// most of its waves repeat a row.  Whole backward, bf16, d 32, H 8, us with
-// rows_qbias and with qbias:
-//   rows per plane     1           2           3           4           8
-//   64 x 160 keys    87, 48      53, 37      44, 35      39, 35      35, 40
-//   64 x 256        169, 90      98, 66      74, 57      66, 56      55, 52
-//   64 x 512        517, 442    315, 310    251, 230    246, 241    201, 202
-//   8 x 160                      17, 16                  17, 18      20, 21
-// (60 rows for three to a plane.)  Four rows pay up to 256 keys where rows_qbias
-// has a workgroup for every CU.  At lengths that are no multiple of 8, where
-// qbias reads the bias and writes dBias element by element, it is level at best
-// (64 x 251, two rows: 110, 105; 64 x 500, one row: 500, 667).
-inline bool few_rows_per_plane(const Problem &p, bool has_bias) {
-    if (!has_bias || p.dtype != 1 || p.D > 32 || p.L % 8 != 0) return false;
-    if (p.rpb <= 3) return true;
-    return p.rpb == 4 && p.L <= 256 && p.N / p.rpb * p.H * ((p.L + 31) / 32) >= 256;
-}
-
 template <typename T, int D, int NKT>
 hipError_t launch_qb_v(const Problem &p, const QbArgs &qa, hipStream_t s) {
     // BV: bias rows split into whole 16-byte groups
     if (p.L % Tr<T>::VEC == 0)
         hipLaunchKernelGGL((qbias_kernel<T, D, NKT, true>), dim3(round8(qa.n_units)), dim3(NKT * 64), 0, s, qa);
     else if constexpr (sizeof(typename Tr<T>::elem) == 2 && D <= 32)
-        return hipErrorInvalidValue;  // excluded by few_rows_per_plane
+        return hipErrorInvalidValue;  // excluded by plan_bwd
     else
         hipLaunchKernelGGL((qbias_kernel<T, D, NKT, false>), dim3(round8(qa.n_units)), dim3(NKT * 64), 0, s, qa);
     return hipGetLastError();
@@ -999,7 +979,7 @@ hipError_t launch_bwd_t(const Problem &p, const BwdPtrs &x, void *ws, const BwdP
     QbArgs qa;
     qa.q = x.q; qa.k = x.k; qa.v = x.v; qa.bias = x.bias; qa.mask = x.mask; qa.lse = x.lse;
     qa.da = ka.da; qa.dsum = ka.dsum; qa.dq = x.dq;
-    const bool direct = few_rows_per_plane(p, x.bias != nullptr);  // one row chunk: the sums are dBias
+    const bool direct = x.bias && plan.direct;  // one row chunk per plane: its sums are dBias
     qa.part = direct ? x.dbias : x.bias ? (float *)(w + plan.off_part) : nullptr;
     qa.L = p.L; qa.rpb = rpb; qa.srow = p.srow; qa.stok = p.stok;
     qa.chunks = plan.chunks; qa.rows_per_chunk = plan.rows_per_chunk;
@@ -1026,6 +1006,40 @@ hipError_t launch_bwd_t(const Problem &p, const BwdPtrs &x, void *ws, const BwdP
 }
 
 }  // namespace
+
+// bf16 up to head_dim 32: whether qbias_kernel with qc row chunks per plane costs
+// no more than rows_qbias_kernel with rc chunks at rows_cost.  The latter has
+// one eight-wave workgroup to a CU, and with fewer rows in a chunk than row
+// slots most of its waves repeat a row; qbias_kernel gives all its waves to one
+// row, two workgroups to a CU up to 256 keys.  In the units of rows_cost (about
+// 0.65 us) a row of qbias_kernel is 2 up to 256 keys and 2.5 past them, a round
+// of its workgroups 2 and 3 more, and a MB of partial planes, written and read,
+// 0.8: fitted to 656 calls of 1 to 256 rows per plane and 136 to 512 keys, on
+// average 0.1 % slower than the better kernel of each and 5 % in all but two.
+// Whole backward, d 32, H 8, us with rows_qbias and with qbias:
+//   rows per plane     1           2           3           4           8
+//   64 x 160 keys    87, 48      53, 37      44, 35      39, 35      35, 40
+//   64 x 256        169, 90      98, 66      74, 57      66, 56      55, 52
+//   64 x 512        517, 442    315, 310    251, 230    246, 241    201, 202
+//   8 x 160                      17, 16                  17, 18      20, 21
+// (60 rows for three to a plane; 16 rows of 256 in one plane 26.6, 25.7.)  At
+// lengths that are no multiple of 8, where qbias reads the bias and writes dBias
+// element by element, it is level at best (64 x 251, two rows: 110, 105;
+// 64 x 500, one row: 500, 667) and not taken.
+static bool qbias_costs_less(const Problem &p, int64_t planes, int64_t rpb, int64_t qc, int64_t rc,
+                             int64_t rows_cost) {
+    if (p.L % 8 != 0) return false;
+    const int64_t nqt = (p.L + 31) / 32;
+    const bool wide = nqt > 8;  // 16 waves, one workgroup to a CU
+    const int64_t slots = wide ? 256 : 512;
+    const int64_t g = (rpb + qc - 1) / qc, c = (rpb + g - 1) / g;
+    const int64_t rounds = (planes * p.H * nqt * c + slots - 1) / slots;
+    const int64_t plane_kb = planes * p.H * p.L * p.L * 4 / 1000;
+    // in thousandths
+    const int64_t q = rounds * (wide ? g * 2500 + 3000 : g * 2000 + 2000) + (c > 1 ? c * plane_kb * 4 / 5 : 0);
+    const int64_t r = rows_cost * 1000 + (rc > 1 ? rc * plane_kb * 4 / 5 : 0);
+    return q <= r;
+}
 
 BwdPlan plan_bwd(const Problem &p, bool has_bias, size_t cap) {
     if (fused_bwd_supported(p, has_bias)) {
@@ -1070,20 +1084,23 @@ BwdPlan plan_bwd(const Problem &p, bool has_bias, size_t cap) {
     // workgroups gain (16 rows over 8 heads: 4 chunks beat 8; one-wave
     // workgroups of 32-key rows gain from every extra chunk instead)
     int64_t chunks = 0;
-    const bool few_rows = few_rows_per_plane(p, has_bias);
-    const bool rows_qbias = rows_qbias_supported(p) && !few_rows;
+    const bool narrow = rows_qbias_supported(p);
     int key_parts = 0;
-    if (few_rows) {
-        chunks = planes > 0 ? 1 : 0;
-    } else if (rows_qbias) {
-        int64_t g = 1;
-        if (planes > 0 && rpb > 0 && nqt > 0) rows_qbias_chunks(p, has_bias, &chunks, &g, &key_parts);
-    } else if (planes > 0 && rpb > 0 && nqt > 0) {
+    if (planes > 0 && rpb > 0 && nqt > 0) {
         const int64_t per_chunk = planes * p.H * nqt * waves * head_halves(p);  // waves per row chunk
         chunks = (target_waves + per_chunk - 1) / per_chunk;
         if (waves >= 8 && chunks > rpb / 4) chunks = rpb / 4;
         if (chunks < 1) chunks = 1;
         if (chunks > rpb) chunks = rpb;
+        if (narrow) {
+            int64_t c = 0;
+            int k = 0;
+            const int64_t cost = rows_qbias_chunks(p, has_bias, &c, &k);
+            if (!has_bias || !qbias_costs_less(p, planes, rpb, chunks, c, cost)) {
+                chunks = c;
+                key_parts = k;
+            }
+        }
     }
     // workspace layout for a given number of row chunks; with a cap, fewer
     // chunks (fewer partial dBias planes, longer qbias workgroups) until it fits
@@ -1107,10 +1124,10 @@ BwdPlan plan_bwd(const Problem &p, bool has_bias, size_t cap) {
         if (has_bias && !bias_direct(p)) off = align256(off + (size_t)(planes * p.H * p.L * p.L * es));
         pl.key_parts = key_parts;
         pl.off_part = off;
-        // (bf16 up to head_dim 32 with one row chunk per plane writes dBias directly)
-        if (has_bias && !rows_qbias && !few_rows) off = align256(off + (size_t)(planes * p.H * c * p.L * p.L) * 4);
-        if (has_bias && rows_qbias && c > 1)
-            off = align256(off + (size_t)(planes * p.H * c * p.L * rows_qbias_pitch(p)) * 4);
+        // bf16 up to head_dim 32 with one row chunk per plane writes dBias itself
+        pl.direct = narrow && c == 1;
+        if (has_bias && !pl.direct)
+            off = align256(off + (size_t)(planes * p.H * c * p.L * (key_parts > 0 ? rows_qbias_pitch(p) : p.L)) * 4);
         pl.total = off;
         return pl;
     };

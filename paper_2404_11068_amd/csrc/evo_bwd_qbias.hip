@@ -461,7 +461,7 @@ bool rows_qbias_supported(const Problem &p) { return p.dtype == 1 && p.D <= 32 &
 
 int rows_qbias_pitch(const Problem &p) { return (int)((p.L + 3) / 4 * 4); }
 
-void rows_qbias_chunks(const Problem &p, bool has_bias, int64_t *chunks, int64_t *rows_per_chunk, int *ks) {
+int64_t rows_qbias_chunks(const Problem &p, bool has_bias, int64_t *chunks, int *ks) {
     const int64_t planes = has_bias ? p.N / p.rpb : 1, rpb = has_bias ? p.rpb : p.N;
     const int64_t nqt = (p.L + 31) / 32;
     const int64_t base = planes * p.H * nqt;  // workgroups per row chunk
@@ -483,8 +483,8 @@ void rows_qbias_chunks(const Problem &p, bool has_bias, int64_t *chunks, int64_t
     }
     const int64_t g = (rpb + bc - 1) / bc;
     *chunks = (rpb + g - 1) / g;
-    *rows_per_chunk = g;
     *ks = bk;
+    return best;
 }
 
 hipError_t launch_rows_qbias(const Problem &p, const BwdPtrs &x, const void *da, const float *dsum, float *part,

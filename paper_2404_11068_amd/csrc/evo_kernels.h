@@ -44,6 +44,7 @@ struct BwdPlan {
     int64_t rows_per_chunk;  // rows handled by one workgroup of the dBias-producing pass
     int64_t n_wg;            // workgroups of the qbias kernel (two-pass plan)
     int key_parts;           // two-pass plan: waves that share a row in the rows_qbias kernel, 0 for the qbias kernel
+    bool direct;             // two-pass plan: the dQ/dBias pass writes dBias itself (no partial planes)
     size_t off_da, off_dsum, off_biast, off_part, total;
 };
 
@@ -83,7 +84,8 @@ hipError_t launch_bwd_fused(const Problem &p, const BwdPtrs &x, void *ws, int64_
 // second pass of the two-pass backward for bf16 at head_dim <= 32 (evo_bwd_qbias.hip)
 bool rows_qbias_supported(const Problem &p);
 int rows_qbias_pitch(const Problem &p);  // floats per row of a partial dBias plane
-void rows_qbias_chunks(const Problem &p, bool has_bias, int64_t *chunks, int64_t *rows_per_chunk, int *key_parts);
+// its row chunks per bias plane and waves per row; returns their cost
+int64_t rows_qbias_chunks(const Problem &p, bool has_bias, int64_t *chunks, int *key_parts);
 hipError_t launch_rows_qbias(const Problem &p, const BwdPtrs &x, const void *da, const float *dsum, float *part,
                           int64_t chunks, int64_t rows_per_chunk, int key_parts, hipStream_t s, Tracer &tr);
 

@@ -25,9 +25,9 @@ def run_named(x, rpb):
 
 
 # The dQ/dBias pass where few rows share a bias plane: (N, L, H, d, rows per
-# plane, kernel).  Up to three rows qbias_kernel (8 waves up to 256 keys, 16
-# past them), which writes dBias itself; four up to 256 keys where rows_qbias
-# has a workgroup for every CU; never at lengths that are no multiple of 8.
+# plane, kernel).  qbias_kernel (8 waves up to 256 keys, 16 past them) where the
+# cost rule finds it no slower, with one row chunk per plane (it then writes
+# dBias itself) and with several; never at lengths that are no multiple of 8.
 FEW = [
     (3, 136, 2, 16, 1, "qbias_kernel<16, 8, true>"),
     (6, 160, 2, 32, 3, "qbias_kernel<32, 8, true>"),
@@ -36,10 +36,12 @@ FEW = [
     (3, 264, 2, 8, 3, "qbias_kernel<8, 16, true>"),
     (2, 512, 1, 32, 1, "qbias_kernel<32, 16, true>"),
     (4, 376, 1, 16, 2, "qbias_kernel<16, 16, true>"),
-    (104, 136, 2, 16, 4, "qbias_kernel<16, 8, true>"),   # 26 planes x 2 heads x 5 query tiles
-    (100, 136, 2, 16, 4, "rows_qbias_kernel<"),          # 25 planes: 250 workgroups
-    (4, 264, 2, 32, 4, "rows_qbias_kernel<"),
-    (5, 136, 2, 32, 5, "rows_qbias_kernel<"),
+    (104, 136, 2, 16, 4, "qbias_kernel<16, 8, true>"),
+    (16, 256, 2, 32, 16, "qbias_kernel<32, 8, true>"),   # four row chunks
+    (27, 200, 5, 32, 9, "qbias_kernel<32, 8, true>"),    # two, the second with fewer rows
+    (100, 136, 2, 16, 4, "rows_qbias_kernel<"),
+    (8, 160, 2, 32, 4, "rows_qbias_kernel<"),
+    (70, 136, 2, 32, 70, "rows_qbias_kernel<"),
     (3, 140, 2, 32, 1, "rows_qbias_kernel<"),
 ]
 
@@ -53,7 +55,7 @@ def test_few_rows_per_bias_plane(case):
     compare(got, oracle_run(x, "bf16", rpb), "bf16", label=str(case))
     ran = [n for n in names if "qbias_kernel" in n]
     assert len(ran) == 1 and ran[0].startswith(kernel), names
-    assert ran[0].startswith(bench.dq_kernel(w, 2) + "<")
+    assert kernel.startswith(bench.dq_kernel(w, 2) + "<")
 
 
 def test_few_rows_without_a_workspace():
