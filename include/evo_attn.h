@@ -30,12 +30,13 @@
  *   calls may be captured into a HIP graph.  Calls return as soon as the work
  *   is enqueued.
  * - Process-wide state, all of it set once: the environment variable
- *   EVO_ATTN_QBIAS_WAVES (a positive integer; default 4096) is read on the
+ *   EVO_ATTN_QBIAS_WAVES (a positive integer) is read on the
  *   first backward plan of the process and fixes, for the rest of the
  *   process, how many waves the two-pass backward's dQ/dBias pass aims for
  *   (and so its row chunks and workspace size: set it before the first
  *   call, since evo_attn_bwd_workspace_size and evo_attn_bwd must see the
- *   same value); and the fixed scratch of evo_attn_bwd_noalloc (below), with
+ *   same value; unset, the pass takes 4096 waves or, in bf16 at head_dim 8, 16
+ *   and 32, the row chunks of the lowest estimated cost); and the fixed scratch of evo_attn_bwd_noalloc (below), with
  *   its per-device address, looked up on the first such call on a device.
  *   One more environment variable is read on every evo_attn_fwd call and
  *   kept nowhere: EVO_ATTN_FWD_ROWS=0 selects the one-(row, head)-per-

@@ -1073,11 +1073,12 @@ BwdPlan plan_bwd(const Problem &p, bool has_bias, size_t cap) {
     // allow two per CU), with as few row chunks as that allows (each chunk
     // costs one partial dBias plane)
     // (read once: the workspace size and the launch must see the same value)
-    static const int64_t target_waves = [] {
+    static const int64_t set_waves = [] {
         const char *env = getenv("EVO_ATTN_QBIAS_WAVES");
         const long v = env ? atol(env) : 0;
-        return v > 0 ? (int64_t)v : (int64_t)4096;
+        return v > 0 ? (int64_t)v : (int64_t)0;
     }();
+    const int64_t target_waves = set_waves > 0 ? set_waves : 4096;
     // With 8-wave or larger workgroups, row chunks of at least four rows:
     // with fewer rows per workgroup the per-workgroup staging of a 256-key row
     // and the reduction of the partial planes cost more than the extra
@@ -1095,7 +1096,7 @@ BwdPlan plan_bwd(const Problem &p, bool has_bias, size_t cap) {
         if (narrow) {
             int64_t c = 0;
             int k = 0;
-            const int64_t cost = rows_qbias_chunks(p, has_bias, &c, &k);
+            const int64_t cost = rows_qbias_chunks(p, has_bias, set_waves, &c, &k);
             if (!has_bias || !qbias_costs_less(p, planes, rpb, chunks, c, cost)) {
                 chunks = c;
                 key_parts = k;

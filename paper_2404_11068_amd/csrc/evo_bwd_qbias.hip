@@ -461,7 +461,7 @@ bool rows_qbias_supported(const Problem &p) { return p.dtype == 1 && p.D <= 32 &
 
 int rows_qbias_pitch(const Problem &p) { return (int)((p.L + 3) / 4 * 4); }
 
-int64_t rows_qbias_chunks(const Problem &p, bool has_bias, int64_t *chunks, int *ks) {
+int64_t rows_qbias_chunks(const Problem &p, bool has_bias, int64_t waves, int64_t *chunks, int *ks) {
     const int64_t planes = has_bias ? p.N / p.rpb : 1, rpb = has_bias ? p.rpb : p.N;
     const int64_t nqt = (p.L + 31) / 32;
     const int64_t base = planes * p.H * nqt;  // workgroups per row chunk
@@ -473,8 +473,14 @@ int64_t rows_qbias_chunks(const Problem &p, bool has_bias, int64_t *chunks, int 
     const int k0 = p.D == 32 ? (nqt <= 7 ? 1 : nqt <= 12 ? 2 : 4) : (nqt <= 8 ? 1 : 2);
     int64_t best = -1, bc = 1;
     int bk = k0;
+    // (waves: the row chunks that bring the grid to as many, at least one row each)
+    int64_t c0 = 1, c1 = rpb < 64 ? rpb : 64;
+    if (waves > 0) {
+        const int64_t c = (waves + base * kRqWaves - 1) / (base * kRqWaves);
+        c0 = c1 = c < rpb ? c : rpb;
+    }
     for (int k = k0; k <= (nqt <= 8 ? 2 : k0); k *= 2) {
-        for (int64_t c = 1; c <= rpb && c <= 64; ++c) {
+        for (int64_t c = c0; c <= c1; ++c) {
             const int64_t g = (rpb + c - 1) / c;
             const int64_t rounds = (base * c + 255) / 256, per = (g + kRqWaves / k - 1) / (kRqWaves / k);
             const int64_t cost = rounds * (per * ((nqt + k - 1) / k) + 6);

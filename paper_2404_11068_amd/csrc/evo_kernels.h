@@ -84,8 +84,9 @@ hipError_t launch_bwd_fused(const Problem &p, const BwdPtrs &x, void *ws, int64_
 // second pass of the two-pass backward for bf16 at head_dim <= 32 (evo_bwd_qbias.hip)
 bool rows_qbias_supported(const Problem &p);
 int rows_qbias_pitch(const Problem &p);  // floats per row of a partial dBias plane
-// its row chunks per bias plane and waves per row; returns their cost
-int64_t rows_qbias_chunks(const Problem &p, bool has_bias, int64_t *chunks, int *key_parts);
+// its row chunks per bias plane and waves per row; returns their cost.  waves: as
+// many as the caller asks the grid to have (0: the cheapest count)
+int64_t rows_qbias_chunks(const Problem &p, bool has_bias, int64_t waves, int64_t *chunks, int *key_parts);
 hipError_t launch_rows_qbias(const Problem &p, const BwdPtrs &x, const void *da, const float *dsum, float *part,
                           int64_t chunks, int64_t rows_per_chunk, int key_parts, hipStream_t s, Tracer &tr);
 

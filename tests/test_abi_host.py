@@ -5,6 +5,8 @@ launched (the fake device addresses are never dereferenced)."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -219,3 +221,25 @@ def test_probe_exported_and_validates():
     assert lib.evo_probe_rate(0, 0, 1, P(FAKE), None) == 1
     assert lib.evo_probe_rate(0, 1, 0, P(FAKE), None) == 1
     assert lib.evo_probe_rate(1, 1, 1, None, None) == 1
+
+
+@pytest.mark.parametrize("dtype,d", [(1, 32), (1, 16), (1, 64), (0, 32)])
+def test_qbias_waves_setting_sets_the_row_chunks(dtype, d):
+    """EVO_ATTN_QBIAS_WAVES fixes the row chunks of the two-pass backward's
+    dQ/dBias pass, and with them the partial dBias planes in the workspace,
+    whichever kernel runs it: 256 rows of 128 or 256 keys over 4 heads in one
+    plane, with 8 waves in all asked for and with 128 times 8 per (query tile, head)."""
+    _lib()
+    L = 256 if dtype else 128
+    planes = 4 * L * L * 4
+    nqt = L // 32
+    code = ("from paper_2404_11068_amd import evo_attn as ea; import ctypes; "
+            "print(ea.load_library().evo_attn_bwd_workspace_size(ctypes.byref("
+            "ea.evo_attn_dims(%d, 4, %d, 0, 256, %d, 256, %d, %d))))" % (dtype, d, L, L * 4 * d, 4 * d))
+    sizes = []
+    for waves in (8, 8 * 128 * nqt * 4):
+        env = dict(os.environ, EVO_ATTN_QBIAS_WAVES=str(waves))
+        sizes.append(int(subprocess.run([sys.executable, "-c", code], env=env, cwd=ROOT, check=True,
+                                        capture_output=True, text=True).stdout))
+    # one chunk needs at most one partial plane per head, 64 chunks and more that many
+    assert sizes[1] - sizes[0] >= 62 * planes, sizes
