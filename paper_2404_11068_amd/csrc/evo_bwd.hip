@@ -842,7 +842,7 @@ hipError_t launch_kv(const KvArgs &ka0, hipStream_t s) {
 // (four groups of two waves against two of one, 16 rows: 256 keys 14.6 and
 // 13.3, 448 keys 42 and 24; two groups of two waves, 32 rows of 256: 22.7
 // and 19.0).  Tile counts that do not divide so take the nearest count that
-// does.
+// does, or run as a larger tile count (launch_kv_d).
 template <typename T, int D, int NKT, bool BV>
 hipError_t launch_kv_g(const KvArgs &ka, hipStream_t s) {
     constexpr int K4 = NKT % 4 == 0 ? 4 : NKT == 6 ? 3 : NKT == 5 || NKT == 10 ? 5 : NKT == 14 ? 7 : 1;
@@ -870,11 +870,17 @@ hipError_t launch_kv_d(const Problem &p, const KvArgs &ka, hipStream_t s) {
     if constexpr (sizeof(typename Tr<T>::elem) == 2 && D <= 32) {
         // 257..512 keys: up to 16-wave workgroups, bf16 with head_dim <= 32
         // only (the staged Q and dA of 512 tokens fill the LDS otherwise)
-        if (nkt == 5) return launch_kv_v<T, D, 5>(p, ka, s);
-        if (nkt == 6) return launch_kv_v<T, D, 6>(p, ka, s);
-        if (nkt > 14) return launch_kv_v<T, D, 16>(p, ka, s);
+        // Five, ten and fourteen tiles split into five and seven groups only: as
+        // many while the CUs hold them all one to each, above that and up to
+        // 64 units the three or four groups of a larger tile count (64 units,
+        // d 32, us of the whole backward: 160 keys 19.9 -> 17.6, 320 keys 29.6
+        // -> 28.5, 448 keys 41.7 -> 34.8).
+        const bool five = ka.n_units * 5 <= 256 || ka.n_units > 64, seven = ka.n_units * 7 <= 256 || ka.n_units > 64;
+        if (nkt == 5 && five) return launch_kv_v<T, D, 5>(p, ka, s);
+        if (nkt == 5 || nkt == 6) return launch_kv_v<T, D, 6>(p, ka, s);
+        if (nkt > 14 || (nkt > 12 && !seven)) return launch_kv_v<T, D, 16>(p, ka, s);
         if (nkt > 12) return launch_kv_v<T, D, 14>(p, ka, s);
-        if (nkt > 10) return launch_kv_v<T, D, 12>(p, ka, s);
+        if (nkt > 10 || (nkt > 8 && !five)) return launch_kv_v<T, D, 12>(p, ka, s);
         if (nkt > 8) return launch_kv_v<T, D, 10>(p, ka, s);
         return launch_kv_v<T, D, 8>(p, ka, s);  // (up to 128 keys: the single-pass backward)
     } else {

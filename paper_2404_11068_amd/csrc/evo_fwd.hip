@@ -765,12 +765,14 @@ hipError_t launch_rows_d(const Problem &p, const FwdPtrs &x, hipStream_t s, int6
 // unit's query tiles are split over two workgroups, over four at 64 units or
 // fewer (each stages the unit's K and V, mostly from the L2 its XCD shares
 // with the unit's other groups; at 128 units two were faster than four).
-// Tile counts that do not divide so take the nearest count that does.
+// Tile counts that do not divide so take the nearest count that does, or run
+// as a larger tile count (launch_d); three tiles are never split (65 to 96 keys,
+// 64 to 480 units, one workgroup against three: 4.4 to 6.3 us against 4.4 to 6.9).
 template <typename T, int D, int NKT, bool BV>
 hipError_t launch_t(const Problem &p, const FwdPtrs &x, hipStream_t s) {
     const int64_t units = p.N * p.H * (D > 32 ? D / 32 : 1);
-    constexpr int Q4 = NKT % 4 == 0 ? 4 : NKT == 3 || NKT == 6 ? 3 : NKT == 5 || NKT == 10 ? 5 : NKT == 14 ? 7 : 1;
-    constexpr int Q2 = NKT < 4 ? Q4 : NKT % 2 == 0 ? 2 : 1;
+    constexpr int Q4 = NKT % 4 == 0 ? 4 : NKT == 6 ? 3 : NKT == 5 || NKT == 10 ? 5 : NKT == 14 ? 7 : 1;
+    constexpr int Q2 = NKT >= 4 && NKT % 2 == 0 ? 2 : 1;
     if constexpr (Q4 > 1) {
         if (units <= 64) return launch_q<T, D, NKT, BV, Q4>(p, x, s);
     }
@@ -803,19 +805,26 @@ hipError_t launch_d(const Problem &p, const FwdPtrs &x, hipStream_t s) {
     // of two only, 384 keys (384 rows, H 4, d 32) ran 123 us against 85, 317
     // keys (317 rows, an odd length, whose bias was read element by element)
     // 210 us against 73.
+    // Five, ten and fourteen tiles split into five and seven groups only: while
+    // the CUs hold them all one to each, later with fewer groups of the next
+    // tile count, or five tiles unsplit past 128 units (us, d 32, as split
+    // by themselves against as taken): 160 keys, 128 units 6.6 (five groups) or
+    // 7.0 (unsplit), 6.0; 192 units 7.2, 7.4; 320 keys, 64 units 10.2, 8.4; 448
+    // keys, 32 units 10.2, 10.4; 64 units 12.0, 11.1.
+    [[maybe_unused]] const int64_t units = p.N * p.H;
     if constexpr (kBf && D <= 32) {
         if (nkt == 3) return launch_t<T, D, 3>(p, x, s);
-        if (nkt == 5) return launch_t<T, D, 5>(p, x, s);
-        if (nkt == 6) return launch_t<T, D, 6>(p, x, s);
+        if (nkt == 5 && (units * 5 <= 256 || units > 128)) return launch_t<T, D, 5>(p, x, s);
+        if (nkt == 5 || nkt == 6) return launch_t<T, D, 6>(p, x, s);
     }
     if (nkt <= 4) return launch_t<T, D, 4>(p, x, s);
     if (nkt <= 8) return launch_t<T, D, 8>(p, x, s);
     // 257..512 keys: up to 16 query tiles, 16 waves (bf16, head_dim <= 32: K
     // and V of 512 keys fit the LDS; the ABI rejects the rest before this point)
     if constexpr (kBf && D <= 32) {
-        if (nkt <= 10) return launch_t<T, D, 10>(p, x, s);
+        if (nkt <= 10 && (units * 5 <= 256 || units > 64)) return launch_t<T, D, 10>(p, x, s);
         if (nkt <= 12) return launch_t<T, D, 12>(p, x, s);
-        if (nkt <= 14) return launch_t<T, D, 14>(p, x, s);
+        if (nkt <= 14 && (units * 7 <= 256 || units > 64)) return launch_t<T, D, 14>(p, x, s);
         return launch_t<T, D, 16>(p, x, s);
     }
     return hipErrorInvalidValue;

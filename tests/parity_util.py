@@ -72,12 +72,17 @@ def kernels_run(fn):
     with profile(activities=[ProfilerActivity.CUDA]) as prof:
         fn()
         torch.cuda.synchronize()
-    names = [e.name.split("::")[-1] if "<" not in e.name else e.name[:e.name.rindex("(")]
-             for e in sorted(prof.events(), key=lambda e: e.time_range.start) if "evo::" in e.name]
-    if not names:
+    events = sorted((e for e in prof.events() if "evo::" in e.name), key=lambda e: e.time_range.start)
+    if not events:
         pytest.skip("the profiler keeps no kernel records here")
-    return [n.replace("void ", "").replace("evo::", "").replace("(anonymous namespace)::", "").replace("bf16_t, ", "")
-            for n in names]
+    drop = ("void ", "(anonymous namespace)::", "evo::", "bf16_t, ")
+    names = []
+    for e in events:
+        n = e.name
+        for d in drop:
+            n = n.replace(d, "")
+        names.append(n[:n.index("(")])
+    return names
 
 
 def compare(got: dict, ref: dict, dtype: str, names=None, label=""):

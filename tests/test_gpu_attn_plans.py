@@ -69,3 +69,32 @@ def test_few_rows_without_a_workspace():
     b = ea.evo_attn_bwd_noalloc(*args, out, lse, dev["dout"], rows_per_bias=2)
     torch.cuda.synchronize()
     assert all(torch.equal(s, t) for s, t in zip(a, b))
+
+
+# Tile counts that split into odd numbers of groups, at the unit counts (rows
+# times heads) where the split or the tile count of the kernel changes: (N, L, H,
+# d, forward kernel, dK/dV kernel).  fwd_kernel<d, tiles, 1, even length, query
+# groups>, kv_kernel<d, tiles, even length, key groups, waves per key tile>.
+SPLITS = [
+    (20, 72, 4, 8, "fwd_kernel<8, 3, 1, true, 1>", None),             # three tiles: never split
+    (17, 67, 3, 16, "fwd_kernel<16, 3, 1, false, 1>", None),
+    (17, 160, 3, 32, "fwd_kernel<32, 5, 1, true, 5>", "kv_kernel<32, 5, true, 5, 2>"),
+    (13, 157, 4, 16, "fwd_kernel<16, 6, 1, false, 3>", "kv_kernel<16, 6, false, 3, 2>"),
+    (32, 134, 4, 8, "fwd_kernel<8, 6, 1, true, 2>", "kv_kernel<8, 5, true, 1, 1>"),
+    (43, 160, 3, 16, "fwd_kernel<16, 5, 1, true, 1>", "kv_kernel<16, 5, true, 1, 1>"),
+    (17, 319, 3, 8, "fwd_kernel<8, 10, 1, false, 5>", "kv_kernel<8, 10, false, 5, 2>"),
+    (16, 290, 4, 16, "fwd_kernel<16, 12, 1, true, 4>", "kv_kernel<16, 12, true, 4, 2>"),
+    (12, 421, 3, 16, "fwd_kernel<16, 14, 1, false, 7>", "kv_kernel<16, 14, false, 7, 2>"),
+    (16, 448, 4, 8, "fwd_kernel<8, 16, 1, true, 4>", "kv_kernel<8, 16, true, 4, 2>"),
+]
+
+
+@pytest.mark.parametrize("case", SPLITS, ids=lambda c: "N%dL%dH%dd%d" % c[:4])
+def test_splits_of_small_calls(case):
+    N, L, H, d, fwd, kv = case
+    w, x = make_inputs(N, L, H, d, "bf16", mask="length", seed=70 + L)
+    print("\n[case]", case, flush=True)
+    got, names = run_named(x, N)
+    compare(got, oracle_run(x, "bf16", N), "bf16", label=str(case))
+    assert fwd in names, names
+    assert kv is None or kv in names, names
