@@ -93,7 +93,8 @@ def dq_kernel(w, es: int) -> str:
     qc = up(rpb, g)
     plane_kb = w.n_rows // rpb * w.n_heads * w.seq_len ** 2 * 4 // 1000
     parts = lambda c: c * plane_kb * 4 // 5 if c > 1 else 0
-    q = up(base * qc, 256 if wide else 512) * (g * 2500 + 3000 if wide else g * 2000 + 2000) + parts(qc)
+    n = up(base * qc, 256)
+    q = (n * (g * 2500 + 3000) if wide else n // 2 * (g * 2000 + 4000) + n % 2 * (g * 1200 + 5000)) + parts(qc)
     return "qbias_kernel" if q <= cost * 1000 + parts(rc) else "rows_qbias_kernel"
 
 

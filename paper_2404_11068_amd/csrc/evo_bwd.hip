@@ -1018,11 +1018,11 @@ hipError_t launch_bwd_t(const Problem &p, const BwdPtrs &x, void *ws, const BwdP
 // one eight-wave workgroup to a CU, and with fewer rows in a chunk than row
 // slots most of its waves repeat a row; qbias_kernel gives all its waves to one
 // row, two workgroups to a CU up to 256 keys.  In the units of rows_cost (about
-// 0.65 us) a row of qbias_kernel is 2 up to 256 keys and 2.5 past them, a round
-// of its workgroups 2 and 3 more, and a MB of partial planes, written and read,
-// 0.8: fitted to 656 calls of 1 to 256 rows per plane and 136 to 512 keys, on
-// average 0.1 % slower than the better kernel of each and 5 % in all but two.
-// Whole backward, d 32, H 8, us with rows_qbias and with qbias:
+// 0.65 us) a row of qbias_kernel is 1.2 for a workgroup alone on its CU, 2 for
+// two together and 2.5 past 256 keys, a round of the workgroups 5, 4 and 3 more,
+// and a MB of partial planes, written and read, 0.8: fitted to 1066 calls of 1
+// to 256 rows per plane and 136 to 512 keys, on average 0.06 % slower than the
+// better kernel of each, 4 % or less in all but one.  Whole backward, d 32, H 8, us with rows_qbias and with qbias:
 //   rows per plane     1           2           3           4           8
 //   64 x 160 keys    87, 48      53, 37      44, 35      39, 35      35, 40
 //   64 x 256        169, 90      98, 66      74, 57      66, 56      55, 52
@@ -1036,13 +1036,13 @@ static bool qbias_costs_less(const Problem &p, int64_t planes, int64_t rpb, int6
                              int64_t rows_cost) {
     if (p.L % 8 != 0) return false;
     const int64_t nqt = (p.L + 31) / 32;
-    const bool wide = nqt > 8;  // 16 waves, one workgroup to a CU
-    const int64_t slots = wide ? 256 : 512;
     const int64_t g = (rpb + qc - 1) / qc, c = (rpb + g - 1) / g;
-    const int64_t rounds = (planes * p.H * nqt * c + slots - 1) / slots;
+    const int64_t n = (planes * p.H * nqt * c + 255) / 256;  // workgroups per CU
     const int64_t plane_kb = planes * p.H * p.L * p.L * 4 / 1000;
     // in thousandths
-    const int64_t q = rounds * (wide ? g * 2500 + 3000 : g * 2000 + 2000) + (c > 1 ? c * plane_kb * 4 / 5 : 0);
+    const int64_t wgs = nqt > 8 ? n * (g * 2500 + 3000)  // (16 waves: one to a CU)
+                                : n / 2 * (g * 2000 + 4000) + n % 2 * (g * 1200 + 5000);
+    const int64_t q = wgs + (c > 1 ? c * plane_kb * 4 / 5 : 0);
     const int64_t r = rows_cost * 1000 + (rc > 1 ? rc * plane_kb * 4 / 5 : 0);
     return q <= r;
 }
