@@ -87,7 +87,7 @@ __device__ __forceinline__ Tr<bf16_t>::K32 ds_transpose(uint16_t *tile, const Tr
 template <int NKT, int NQR>
 constexpr int kLdsBiasTiles = NKT > NQR ? NKT - NQR : 0;
 
-template <int D, int NKT, bool HB, bool BV, int NQR>
+template <int D, int NKT, bool HB, int BM, int NQR>
 __global__ void __launch_bounds__(NKT * 64) bwd_fused_kernel(FusedArgs a) {
     using E = uint16_t;
     using K32 = Tr<bf16_t>::K32;
@@ -208,11 +208,26 @@ __global__ void __launch_bounds__(NKT * 64) bwd_fused_kernel(FusedArgs a) {
             }
         }
         // first query tile's bias rows
-        BiasRaw<!BV> bnext;
+        BiasRaw<BM == 2> bnext;
         if constexpr (HB) bnext.load(rb.r, boff);
         // the rows of query tile qt as the A operand of the bias product; rows
-        // past L must be zeros (even lengths: past the end of the resource)
+        // past L must be zeros (even lengths: past the end of the resource), and
+        // keys past L as well: a -inf there, the next row's, would turn the
+        // whole row's tile into NaN.  (At multiples of 8 they are not cleared.)
         auto bias_rows = [&](int qt) {
+            if constexpr (BM == 1) {
+                K32 f = bnext.get(boff, true, 0);
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const u32x4 w = __builtin_bit_cast(u32x4, f.v[t]);
+                    const uint32_t x[4] = {w.x, w.y, w.z, w.w};
+                    uint32_t y[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) y[j] = kt * 32 + 16 * t + 8 * h2 + 2 * j < L ? x[j] : 0u;
+                    f.v[t] = __builtin_bit_cast(bf16x8, u32x4{y[0], y[1], y[2], y[3]});
+                }
+                return f;
+            }
             const bool full = kt * 32 + 32 <= L && qt * 32 + 32 <= L;
             return bnext.get(boff, full, qt * 32 + sig(n) < L ? L - kt * 32 - 8 * h2 : 0);
         };
@@ -565,10 +580,10 @@ __global__ void __launch_bounds__(256) dbias_tiles_reduce_kernel(const float *__
 // query tiles whose dBias accumulators stay in registers (the rest go to LDS)
 template <int D, int NKT> constexpr int kFusedNQR = NKT <= 4 ? NKT : 5;
 
-template <int D, int NKT, bool HB, bool BV>
+template <int D, int NKT, bool HB, int BM>
 hipError_t launch_fused_t(const FusedArgs &fa, hipStream_t s) {
     const unsigned grid = (unsigned)((fa.n_units + 7) / 8 * 8);  // XCD-aware order; surplus workgroups exit
-    hipLaunchKernelGGL((bwd_fused_kernel<D, NKT, HB, BV, kFusedNQR<D, NKT>>), dim3(grid), dim3(NKT * 64), 0, s, fa);
+    hipLaunchKernelGGL((bwd_fused_kernel<D, NKT, HB, BM, kFusedNQR<D, NKT>>), dim3(grid), dim3(NKT * 64), 0, s, fa);
     return hipGetLastError();
 }
 
@@ -587,10 +602,11 @@ constexpr bool kFusedBias = NKT <= 4 || D == 8;
 
 template <int D, int NKT>
 hipError_t launch_fused_n(const Problem &p, const FusedArgs &fa, hipStream_t s) {
-    if (!fa.bias) return launch_fused_t<D, NKT, false, true>(fa, s);
+    if (!fa.bias) return launch_fused_t<D, NKT, false, 0>(fa, s);
     if constexpr (kFusedBias<D, NKT>) {
-        if (p.L % 2 == 0) return launch_fused_t<D, NKT, true, true>(fa, s);
-        if constexpr (NKT <= 4) return launch_fused_t<D, NKT, true, false>(fa, s);
+        if (p.L % 8 == 0) return launch_fused_t<D, NKT, true, 0>(fa, s);
+        if constexpr (NKT <= 4)
+            return p.L % 2 == 0 ? launch_fused_t<D, NKT, true, 1>(fa, s) : launch_fused_t<D, NKT, true, 2>(fa, s);
     }
     return hipErrorInvalidValue;  // excluded by fused_bwd_supported
 }

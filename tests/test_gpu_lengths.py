@@ -111,3 +111,30 @@ def test_minus_inf_bias_leaves_a_pair_out(L, d):
     torch.cuda.synchronize()
     for name, a, b in zip(("out", "lse", "dq", "dk", "dv", "dgate", "dbias"), *res):
         assert torch.isfinite(b).all() and torch.equal(a, b), (L, d, name)
+
+
+@pytest.mark.parametrize("L,d", [(18, 16), (34, 32), (66, 8), (90, 16), (122, 32), (126, 8)])
+def test_minus_inf_stays_in_its_row(L, d):
+    """Up to 128 keys a pair bias of -inf gives NaN in its own query row's tile (the
+    bias enters through a matrix product).  At lengths that are no multiple of 8 it
+    must not reach the row before it, whose padded keys lie where it is stored: with -inf at the first key of every
+    other row, the rows between them and the keys of the last tile give the bits of
+    a very low finite bias."""
+    from paper_2404_11068_amd import evo_attn as ea
+    N, H = 3, 2
+    w, x = make_inputs(N, L, H, d, "bf16", seed=80 + L, mask="none")
+    print("\n[case] -inf in the next row", L, d, flush=True)
+    dev = {n: to_device(x[n], "bf16") for n in ("q", "k", "v", "gate", "bias", "dout")}
+    last = (L - 1) // 32 * 32
+    res = []
+    for low in (-1e30, float("-inf")):
+        bias = dev["bias"].clone()
+        bias[..., 1::2, 0] = low
+        args = (dev["q"], dev["k"], dev["v"], dev["gate"], bias, None)
+        out, lse = ea.evo_attn_fwd(*args, rows_per_bias=N)
+        dq, dk, dv, dg, db = ea.evo_attn_bwd(*args, out, lse, dev["dout"], rows_per_bias=N)
+        tiles = (dk[:, last:], dv[:, last:]) if last else ()
+        res.append((out, lse, dg, dq[:, ::2], db[..., ::2, :]) + tiles)
+    torch.cuda.synchronize()
+    for i, (a, b) in enumerate(zip(*res)):
+        assert torch.isfinite(b).all() and torch.equal(a, b), (L, d, i)
