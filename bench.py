@@ -149,6 +149,16 @@ def kernel_model(w, es: int, ws_bytes: int):
     return ks
 
 
+def kernel_slots(w, es: int, n_model: int, slots):
+    """Of the traced backward's intervals, those that bracket a kernel: without the
+    transpose's where the two-pass backward reads the bias as it is, and without
+    those after the last kernel (no reduction where dBias is written directly)."""
+    slots = list(slots)
+    if w.bias and not fused_backward(w, es) and not bias_transposed(w, es):
+        del slots[0]
+    return slots[:n_model - 1]
+
+
 def algorithmic_bytes(w, es: int):
     """Bytes the forward and the backward must move at least once."""
     tok = w.n_rows * w.seq_len * w.n_heads * w.head_dim * es
@@ -289,12 +299,9 @@ def main():
     bwd_warm = [l_[0].elapsed_time(l_[-1]) for l_ in bev]
     fwd_ms = float(np.mean(fwd_warm))
     bwd_ms = float(np.mean(bwd_warm))
-    kern_ms = [fwd_ms] + [float(np.mean([l_[j].elapsed_time(l_[j + 1]) for l_ in bev])) for j in range(nk)]
     model = kernel_model(w, es, ws.numel())
-    if fused_backward(w, es):
-        kern_ms = kern_ms[:len(model)]  # the slots after the last kernel bracket nothing
-    elif w.bias and not bias_transposed(w, es):
-        del kern_ms[1]  # the transpose slot brackets no kernel
+    kern_ms = [fwd_ms] + kernel_slots(
+        w, es, len(model), [float(np.mean([l_[j].elapsed_time(l_[j + 1]) for l_ in bev])) for j in range(nk)])
 
     # cold mode: a 512 MiB scratch buffer is written before every timed call
     # (outside the events), which evicts the inputs from L2 and the Infinity

@@ -178,9 +178,11 @@ int evo_attn_bwd(const evo_attn_dims *dims, const void *q, const void *k, const 
  * i-th kernel, so event pairs bracket single kernels.  Kernel order in this
  * version: [pair-bias transpose], dK/dV pass, dQ/dBias pass, [dBias reduce]
  * (bracketed entries only when bias != NULL).  The transpose runs only for
- * fp32; otherwise the dK/dV pass reads
- * the bias as it is and events[0] and events[1] bracket no kernel (the slot is
- * kept so that the event count depends on has_bias alone).  n_events must be at least
+ * fp32; a bf16 dK/dV pass reads the bias as it is and events[0] and events[1]
+ * bracket no kernel (the slot is kept so that the event count depends on
+ * has_bias alone).  Events after the last kernel bracket nothing: the reduce's
+ * where dBias is written directly (one row chunk per bias plane), and the later
+ * ones of the single-pass backward (one kernel and its reduce).  n_events must be at least
  * evo_attn_bwd_kernel_count(bias != NULL) + 1 and every handle non-NULL,
  * else EVO_ERR_INVALID_ARG.  Meant for benchmarks; recording events costs a
  * few microseconds per call.

@@ -94,3 +94,26 @@ def test_kernel_model_adds_up(name):
     else:
         # the two passes both read Q, K, V, LSE, bias and mask: at least the step's bytes
         assert sum(k[1] for k in ks[1:]) >= bwd
+
+
+@pytest.mark.parametrize("N,L,d,rpb,planes,names", [
+    (4, 200, 32, 2, 0, ["fwd_kernel", "kv_kernel", "qbias_kernel"]),
+    (3, 163, 32, 1, 0, ["fwd_kernel", "kv_kernel", "rows_qbias_kernel"]),
+    (40, 163, 32, 40, 2, ["fwd_kernel", "kv_kernel", "rows_qbias_kernel", "dbias_reduce"]),
+    (40, 96, 32, 40, 0, ["fwd_kernel", "bwd_fused_kernel"]),
+    (40, 96, 32, 40, 2, ["fwd_kernel", "bwd_fused_kernel", "dbias_tiles_reduce"]),
+])
+def test_traced_intervals_map_to_the_kernels(N, L, d, rpb, planes, names):
+    """Every kernel of the model has one interval of the traced backward, in order,
+    where the transpose and the reduction run and where they do not (their
+    intervals bracket nothing, here -1)."""
+    w = W.Workload("adhoc", N, L, 2, d, "bf16", True, rpb)
+    two_pass = L > 128
+    ws = planes * 2 * L * L * 4 if not two_pass else bench._align(N * L * 2 * d * 2) + bench._align(N * 2 * L * 4) + \
+        planes * 2 * L * L * 4
+    model = bench.kernel_model(w, 2, ws)
+    assert [m[0] for m in model] == names
+    slots = ([-1.0, 1.0, 2.0] if two_pass else [1.0]) + ([3.0] if planes else [])
+    slots += [-1.0] * (4 - len(slots))
+    got = bench.kernel_slots(w, 2, len(model), slots)
+    assert len(got) == len(model) - 1 and min(got) > 0.0

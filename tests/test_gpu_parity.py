@@ -319,14 +319,16 @@ def test_unsupported_shapes_raise():
         ea.evo_attn_fwd(q, q, q)
 
 
-@pytest.mark.parametrize("dtype,L", [("bf16", 96), ("bf16", 90), ("f32", 64)])
-def test_traced_backward_matches_plain(dtype, L):
-    """The profiling entry point gives the same bits as the plain backward, on
-    both bias paths (a bf16 bias of whole 16-byte rows is read directly; fp32
-    and other lengths go through the transpose kernel), and its events bracket
-    non-negative intervals."""
-    w, x = make_inputs(3, L, 2, 32, dtype, seed=31 + L)
-    print("\n[case] traced backward", dtype, L, flush=True)
+@pytest.mark.parametrize("dtype,L,N,rpb", [("bf16", 96, 3, 3), ("bf16", 90, 3, 3), ("f32", 64, 3, 3),
+                                           ("bf16", 200, 4, 2), ("bf16", 163, 3, 1), ("bf16", 163, 40, 40)])
+def test_traced_backward_matches_plain(dtype, L, N, rpb):
+    """The profiling entry point gives the same bits as the plain backward, and its
+    events bracket non-negative intervals: the single pass (96 and 90 keys), fp32
+    through the transpose kernel, and the bf16 two passes, which read the bias
+    directly, with one row chunk per plane (no reduction) by either dQ/dBias
+    kernel and with several."""
+    w, x = make_inputs(N, L, 2, 32, dtype, seed=31 + L, rpb=rpb)
+    print("\n[case] traced backward", dtype, L, N, rpb, flush=True)
     dev = {n: to_device(x[n], dtype) for n in ("q", "k", "v", "gate", "bias", "dout")}
     mask = torch.from_numpy(x["mask"]).cuda()
     args = (dev["q"], dev["k"], dev["v"], dev["gate"], dev["bias"], mask)
