@@ -1018,7 +1018,7 @@ def measured_traffic(kernel: str, workload: str):
 
 # device sources of each kernel family (a change to any of them invalidates
 # the family's recorded counters)
-KERNEL_SOURCES = {"attn": ("evo_frag.h", "evo_fwd.hip", "evo_bwd.hip", "evo_bwd_fused.hip"),
+KERNEL_SOURCES = {"attn": ("evo_frag.h", "evo_fwd.hip", "evo_bwd.hip", "evo_bwd_qbias.hip", "evo_bwd_fused.hip"),
                   "ln": ("evo_frag.h", "evo_ln.hip"),
                   "proj": ("evo_frag.h", "evo_proj.hip"),
                   "proj_bwd": ("evo_frag.h", "evo_proj_bwd.hip"),

@@ -117,3 +117,12 @@ def test_traced_intervals_map_to_the_kernels(N, L, d, rpb, planes, names):
     slots += [-1.0] * (4 - len(slots))
     got = bench.kernel_slots(w, 2, len(model), slots)
     assert len(got) == len(model) - 1 and min(got) > 0.0
+
+
+def test_every_kernel_source_belongs_to_a_family():
+    """The recorded counters of a kernel hold while the sources of its family hash
+    to what they did: every file with kernels is in a family (the rate probes
+    have no counters)."""
+    csrc = os.path.join(ROOT, "paper_2404_11068_amd", "csrc")
+    files = {f for f in os.listdir(csrc) if f.endswith(".hip")} - {"evo_probe.hip"}
+    assert files == {f for fam in bench.KERNEL_SOURCES.values() for f in fam if f.endswith(".hip")}
