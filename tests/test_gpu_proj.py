@@ -112,13 +112,15 @@ def test_empty():
 
 
 # ---- backward ---------------------------------------------------------------
-# Tolerances: dx (bf16): per element 4 x the shift the bf16 rounding of dY
-# can cause (2^-9 rstd times |w dY| plus the row means of |w dY| and
-# |w dY xhat| |xhat|) plus 2^-8 |ref|, and 1e-2 normwise; dweight (fp32 sums over R
+# Tolerances: dx (bf16, from dY kept in fp32): per element the rounding of the
+# output, 2^-8 |ref|, plus (F + 2C + 64) 2^-24 for the additions behind it (F of
+# dY, the row means over C channels, the epilogue) times the absolute terms
+# rstd |w| sum |dout||W| and their row means, plus what an error of C 2^-24
+# max|x| in the row's mean moves xhat by, and 5e-3 normwise; dweight (fp32 sums over R
 # tokens of products whose y factor was rounded to bf16): normwise 5e-3 and
 # element-wise 5e-3|ref| + 5e-3 max|ref|; dbias (exact bf16 inputs, fp32
-# sums): 1e-5 relative + 1e-5 max; dln_weight, dln_bias (sums of bf16-rounded
-# dY terms): normwise 5e-3, element-wise 1e-2|ref| + 5e-3 max|ref|.
+# sums): 1e-5 relative + 1e-5 max; dln_weight, dln_bias (fp32 sums of fp32 dY
+# terms): 1e-4 normwise, 1e-4 |ref| + 1e-4 max|ref| per element.
 
 
 def run_bwd(w, d, label, seed=0):
@@ -138,34 +140,33 @@ def run_bwd(w, d, label, seed=0):
                                   W.as_float64(d["weight"], "bf16"), [W.as_float64(a, "bf16") for a in douts_np],
                                   w.eps)
     rdx, rdlw, rdlb, rdW, rdb = ref
-    # dx: the kernel rounds dY to bf16 before the LayerNorm backward, which
-    # moves dx[r, c] by up to rstd_r |w_c| |dY_rc| 2^-9 whatever the size of
-    # dx itself; allow 4x that per element plus the output's own rounding
     xf = W.as_float64(d["x"], "bf16")
     _, _, rrstd = oracle.layernorm_forward(xf, None, None, w.eps)
     Wf = W.as_float64(d["weight"], "bf16")
     HD = w.proj_dim
-    dY = sum(W.as_float64(douts_np[p_], "bf16") @ Wf[p_ * HD:(p_ + 1) * HD] for p_ in range(w.n_proj))
-    # (the row means of g = w dY and g xhat in the LayerNorm backward carry
-    # the same relative rounding, averaged over the row)
+    terms = sum(np.abs(W.as_float64(douts_np[p_], "bf16")) @ np.abs(Wf[p_ * HD:(p_ + 1) * HD])
+                for p_ in range(w.n_proj))
     _, rmean, _ = oracle.layernorm_forward(xf, None, None, w.eps)
     xhat = (xf - rmean[:, None]) * rrstd[:, None]
-    g = np.abs(d["ln_weight"])[None, :] * np.abs(dY)
-    row = g.mean(axis=1)[:, None] + np.abs(xhat) * (g * np.abs(xhat)).mean(axis=1)[:, None]
-    bound = 4 * 2.0 ** -9 * rrstd[:, None] * (g + row) + 2.0 ** -8 * np.abs(rdx)
+    g = np.abs(d["ln_weight"])[None, :] * terms
+    gm, gxm = g.mean(axis=1)[:, None], (g * np.abs(xhat)).mean(axis=1)[:, None]
+    ex = rrstd[:, None] * w.c_in * 2.0 ** -24 * np.abs(xf).max(axis=1)[:, None]
+    bound = ((w.n_proj * HD + 2 * w.c_in + 64) * 2.0 ** -24 * rrstd[:, None] * (g + gm + np.abs(xhat) * gxm)
+             + rrstd[:, None] * ex * (gxm + np.abs(xhat) * gm) + 2.0 ** -8 * np.abs(rdx))
     gdx = to_f64(dx).reshape(rdx.shape)
     err = np.abs(gdx - rdx)
     i = int(np.argmax(err - bound - 1e-6))
+    print("  dx: largest error / bound %.2f" % float((err / (bound + 1e-6)).max()), flush=True)
     assert (err <= bound + 1e-6).all(), (label, "dx err %.3g at ref %.3g (bound %.3g)" %
                                          (err.flat[i], rdx.flat[i], bound.flat[i]))
     rel = np.linalg.norm(gdx - rdx) / np.linalg.norm(rdx)
-    assert rel <= 1e-2, (label, "dx normwise %.3g" % rel)
+    assert rel <= 5e-3, (label, "dx normwise %.3g" % rel)
     m = np.abs(rdW).max()
     _check(label + " dW", to_f64(dW), rdW, atol=5e-3 * m, rtol=5e-3, norm=5e-3)
     if db is not None:
         _check(label + " dbias", to_f64(db), rdb, atol=1e-5 * np.abs(rdb).max(), rtol=1e-5, norm=1e-5)
     for nm, g, r in (("dln_w", dlw, rdlw), ("dln_b", dlb, rdlb)):
-        _check(label + " " + nm, to_f64(g), r, atol=5e-3 * np.abs(r).max(), rtol=1e-2, norm=5e-3)
+        _check(label + " " + nm, to_f64(g), r, atol=1e-4 * np.abs(r).max(), rtol=1e-4, norm=1e-4)
     # the saved normalised input is the forward's bf16 LayerNorm
     yref, _, _ = oracle.layernorm_forward(W.as_float64(d["x"], "bf16"), d["ln_weight"], d["ln_bias"], w.eps)
     _check(label + " y", to_f64(y), yref, norm=5e-3)
