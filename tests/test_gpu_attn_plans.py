@@ -98,3 +98,62 @@ def test_splits_of_small_calls(case):
     compare(got, oracle_run(x, "bf16", N), "bf16", label=str(case))
     assert fwd in names, names
     assert kv is None or kv in names, names
+
+
+# The dQ/dBias kernel's variants, rows_qbias_kernel<d, key tiles per wave, waves
+# per row>: (N, L, H, d, rows per plane, tiles, waves).  Every one that the plan
+# can take, with rows that leave the last chunk's row slots partly empty.
+ROWS_QBIAS = [
+    # one wave per row (eight rows in flight, no barrier in the row loop)
+    (49, 131, 4, 8, 49, 5, 1), (41, 163, 4, 8, 41, 6, 1), (73, 197, 2, 8, 73, 7, 1), (41, 229, 3, 8, 41, 8, 1),
+    (49, 142, 4, 16, 49, 5, 1), (41, 179, 4, 16, 41, 6, 1), (73, 222, 2, 16, 73, 7, 1), (41, 250, 3, 16, 41, 8, 1),
+    (49, 157, 4, 32, 49, 5, 1), (41, 190, 4, 32, 41, 6, 1), (73, 198, 2, 32, 73, 7, 1),
+    # two
+    (5, 163, 1, 8, 5, 3, 2), (6, 229, 2, 8, 3, 4, 2), (5, 290, 1, 8, 5, 5, 2), (4, 350, 2, 8, 2, 6, 2),
+    (5, 389, 2, 8, 5, 7, 2), (3, 490, 1, 8, 1, 8, 2),
+    (5, 190, 1, 16, 5, 3, 2), (6, 250, 2, 16, 3, 4, 2), (5, 261, 1, 16, 5, 5, 2), (4, 383, 2, 16, 2, 6, 2),
+    (5, 418, 2, 16, 5, 7, 2), (3, 511, 1, 16, 1, 8, 2),
+    (5, 131, 1, 32, 5, 3, 2), (6, 197, 2, 32, 3, 4, 2), (5, 319, 1, 32, 5, 5, 2), (4, 322, 2, 32, 2, 6, 2),
+    # four
+    (5, 389, 1, 32, 5, 4, 4), (3, 453, 2, 32, 1, 4, 4),
+]
+
+
+@pytest.mark.parametrize("case", ROWS_QBIAS, ids=lambda c: "d%d_tiles%d_waves%d_N%dL%d" % (c[3], c[5], c[6], c[0], c[1]))
+def test_rows_qbias_variants(case):
+    N, L, H, d, rpb, tiles, waves = case
+    w, x = make_inputs(N, L, H, d, "bf16", rpb=rpb, mask="length" if L % 2 else "bernoulli", seed=90 + L)
+    print("\n[case]", case, flush=True)
+    got, names = run_named(x, rpb)
+    compare(got, oracle_run(x, "bf16", rpb), "bf16", label=str(case))
+    assert "rows_qbias_kernel<%d, %d, %d>" % (d, tiles, waves) in names, names
+
+
+# The one-unit forward and the dK/dV pass with two groups per unit (65 to 511
+# units) and with one (from 512), at every tile count that has a kernel of its own:
+# (N, L, H, d, tiles, forward groups, dK/dV tiles, groups).  Planes of eight rows,
+# compared in the first, a middle and the last plane.
+GROUPS = [
+    (32, 163, 4, 16, 6, 2, 6, 2), (32, 197, 4, 32, 8, 2, 8, 2), (32, 290, 4, 8, 10, 2, 10, 2),
+    (32, 347, 4, 16, 12, 2, 12, 2), (32, 418, 4, 8, 14, 2, 14, 2), (32, 511, 4, 16, 16, 2, 16, 2),
+    (24, 317, 4, 32, 10, 2, 10, 2), (24, 384, 4, 32, 12, 2, 12, 2),
+    (128, 131, 4, 16, 5, 1, 5, 1), (128, 162, 4, 32, 6, 1, 6, 1), (128, 251, 4, 8, 8, 1, 8, 1),
+    (128, 319, 4, 8, 10, 1, 10, 1), (128, 322, 4, 16, 12, 1, 12, 1), (128, 447, 4, 8, 14, 1, 14, 1),
+    (128, 490, 4, 8, 16, 1, 16, 1), (136, 317, 4, 32, 10, 1, 10, 1), (136, 384, 4, 32, 12, 1, 12, 1),
+]
+
+
+@pytest.mark.parametrize("case", GROUPS, ids=lambda c: "N%dL%dH%dd%d" % c[:4])
+def test_group_variants(case):
+    N, L, H, d, ft, fg, kt, kg = case
+    w, x = make_inputs(N, L, H, d, "bf16", rpb=8, mask="length", seed=30 + L)
+    print("\n[case]", case, flush=True)
+    got, names = run_named(x, 8)
+    for plane in (0, N // 16, N // 8 - 1):
+        r = slice(plane * 8, plane * 8 + 8)
+        sub = {n: v[r] if n != "bias" else v[plane:plane + 1] for n, v in x.items()}
+        cut = {n: v[r] if n != "dbias" else v[plane:plane + 1] for n, v in got.items()}
+        compare(cut, oracle_run(sub, "bf16", 8), "bf16", label=str((case, plane)))
+    even = "true" if L % 2 == 0 else "false"
+    assert "fwd_kernel<%d, %d, 1, %s, %d>" % (d, ft, even, fg) in names, names
+    assert "kv_kernel<%d, %d, %s, %d, 1>" % (d, kt, even, kg) in names, names
