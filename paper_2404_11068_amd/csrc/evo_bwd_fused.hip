@@ -123,7 +123,7 @@ __global__ void __launch_bounds__(NKT * 64) bwd_fused_kernel(FusedArgs a) {
     const int L = (int)a.L;
     const int nqt = (L + 31) / 32;
     // unit -> (plane b, row chunk, head), head fastest: the heads of one
-    // chunk land on one XCD (xcd_unit) and share the token cache lines
+    // chunk land on one XCD (xcd_unit32) and share the token cache lines
     const uint32_t unit = xcd_unit32(blockIdx.x, gridDim.x);
     if (unit >= (uint32_t)a.n_units) return;
     const int hh = (int)(unit % (uint32_t)a.H);
@@ -634,8 +634,9 @@ bool fused_bwd_supported(const Problem &p, bool has_bias) {
     return nkt <= 4 || (p.D == 8 && p.L % 8 == 0);
 }
 
-// rows per chunk and chunk count of the fused backward: about 2048 waves in
-// all, each chunk of a plane's rows one workgroup per head
+// rows per chunk and chunk count of the fused backward: each chunk of a plane's
+// rows one workgroup per head, 2048 waves in all with the tile count rounded up
+// to a power of two (so about 1536 at 3 and 6 tiles, 1280 at 5, 1792 at 7)
 void fused_bwd_chunks(const Problem &p, bool has_bias, int64_t *chunks, int64_t *rows_per_chunk) {
     const int64_t planes = has_bias ? p.N / p.rpb : p.N;
     const int64_t rpb = has_bias ? p.rpb : 1;

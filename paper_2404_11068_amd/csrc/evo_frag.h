@@ -528,14 +528,8 @@ __device__ __forceinline__ f32x16 zero16() {
 
 // XCD-aware unit index: consecutive units land on the same XCD (workgroups
 // are dispatched round-robin over the 8 XCDs), so the heads of one row share
-// that XCD's L2.
-__device__ __forceinline__ int64_t xcd_unit(int64_t b, int64_t nb) {
-    if (nb % 8 != 0) return b;
-    return (b % 8) * (nb / 8) + b / 8;
-}
-
-// the same in 32 bits (64-bit divisions of the unit index by run-time counts
-// took over a thousand scalar instructions at the start of every workgroup)
+// that XCD's L2.  (32 bits: divisions of a 64-bit unit index by run-time counts
+// took over a thousand scalar instructions at the start of every workgroup.)
 __device__ __forceinline__ uint32_t xcd_unit32(uint32_t b, uint32_t nb) {
     if (nb % 8 != 0) return b;
     return (b % 8) * (nb / 8) + b / 8;

@@ -55,16 +55,15 @@ inline int proj_bwd_fb(int C, int HD, int P) {
     return 32;
 }
 
-// tokens per workgroup of the dY pass: 128, fewer (down to eight 32 x 32 tiles,
-// one per wave) while the workgroups would leave CUs idle.  At 128 channels
-// always 64: with 128, two workgroups no longer share a CU (100000 tokens x 128:
+// tokens per workgroup of the dY pass: 128 (at 64 channels eight 32 x 32 tiles,
+// one per wave), at 256 channels fewer, down to the same eight tiles, while the
+// workgroups would leave CUs idle.  At 128 channels always 64: with 128, two workgroups no longer share a CU (100000 tokens x 128:
 // backward 88.5 -> 79.6 us, as a plain layer 44.7 -> 39.5); at 256 channels 64
 // would read the weight twice as often (32768 x 256: 77.5 against 69.8 us).
 inline int dy_block_tokens(int64_t R, int C) {
-    const int least = C >= 256 ? 32 : C >= 128 ? 64 : 128;
-    if (C == 128) return 64;
+    if (C < 256) return C == 128 ? 64 : 128;
     int tm = 128;
-    while (tm > least && (R + tm - 1) / tm < 256) tm /= 2;
+    while (tm > 32 && (R + tm - 1) / tm < 256) tm /= 2;
     return tm;
 }
 
