@@ -1,5 +1,6 @@
 // evo_bwd_qbias.hip -- second pass of the two-pass attention backward (dQ and
-// dBias) for bf16 at head_dim 8 / 16 / 32, gfx950.
+// dBias) for bf16 at head_dim 8 / 16 / 32, gfx950, where plan_bwd does not find
+// qbias_kernel (evo_bwd.hip) cheaper.
 //
 // One workgroup of eight waves per (bias plane, head, 32-query tile, chunk of
 // rows).  The waves take rows of their own (KS = 1) or share a row between
@@ -16,15 +17,16 @@
 // in wave order through LDS and leave as one partial dBias tile per chunk (or,
 // with one chunk, as dBias).
 //
-// Why: the kernel this replaces for bf16 up to head_dim 32 gave each of a
-// workgroup's waves one key tile of one row, staged K and V of the row through
-// registers, and summed dQ over all waves behind two barriers per row.
+// Why: qbias_kernel gives each of a workgroup's waves one key tile of one row,
+// stages K and V of the row through registers, and sums dQ over all waves
+// behind two barriers per row, which pays only where a workgroup has few rows.
 // Measured (event-timed, MI355X, bf16, d 32, H 4, a bias shared by all rows):
 //   256 rows x 160 keys   39.6 -> 24.7 us     384 x 384   280 -> 132-139 us
 //   256 x 224             56.4 -> 36 us       317 x 317   206 -> 75 us
-//   256 x 256             48 -> 43 us         256 x 512   162 -> 156 us
+//   256 x 256             48 -> 41 us         256 x 512   162 -> 156 us
 // What bounds it now: 0.6 ns per 32 x 32 tile on the chip against about 0.3 of
-// issue (VALU busy a third of the time, matrix unit an eighth).  Without the
+// issue (VALU busy a third of the time, matrix unit a ninth, waves waiting 0.38
+// of theirs).  Without the
 // loads of K and V a 384-key call still takes two thirds of its time, without
 // the exponentials or the dQ product all of it: two waves per SIMD, all that
 // the accumulators leave room for, do not cover the LDS and matrix-unit
