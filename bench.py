@@ -870,7 +870,7 @@ GRAPH_WORKLOADS = {
 def graph_bench(torch, args):
     """One MSA-row-attention step (LayerNorm + q/k/v/g projections, pair bias,
     attention forward, output projection, and the backward of each: 8 C-ABI
-    calls, 17 kernels) run eagerly through the Python binding and replayed
+    calls, 15 kernels) run eagerly through the Python binding and replayed
     from the HIP graph cache.
     `value` is graphed steps per second; the eager rate, the host time to
     enqueue one step and the speedup are reported beside it."""

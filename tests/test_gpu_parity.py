@@ -70,7 +70,8 @@ SMALL = [
     (3, 200, 2, 8, "bf16", dict(rpb=1)),
     (5, 256, 3, 8, "bf16", dict(bias=False, gate=False)),
     (4, 256, 2, 32, "bf16", dict(bias=False, mask="length")),
-    # 257..512 keys (bf16, head_dim <= 32): 16-wave workgroups, two-pass backward
+    # 257..512 keys (bf16, head_dim <= 32): two-pass backward, the qbias kernel
+    # at three rows or fewer per plane
     (3, 384, 2, 32, "bf16", dict()),
     (2, 512, 2, 32, "bf16", dict(mask="length")),
     (3, 512, 2, 8, "bf16", dict(p=0.2)),
@@ -91,8 +92,8 @@ def test_small_ragged_parity(case):
 
 
 # Shapes that select the row-walking forward (all rows under one bias plane,
-# bf16, L a multiple of 8, at most 256 keys, at least two (row, head) units
-# per resident workgroup: 256 * 8 / (key tiles) workgroups): it must produce
+# bf16, head_dim up to 32, at most 256 keys, at least two (row, head) units per
+# resident workgroup: 256 * floor(8 / key tiles) workgroups): it must produce
 # the bits of the one-unit kernel, which the environment switch
 # EVO_ATTN_FWD_ROWS=0 selects.  The full-size workloads with a shared bias
 # (MSA row, triangle, extra-MSA) run it against the oracle in
