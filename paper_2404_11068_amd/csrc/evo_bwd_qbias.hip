@@ -485,6 +485,7 @@ int64_t rows_qbias_chunks(const Problem &p, bool has_bias, int64_t waves, int64_
         for (int64_t c = c0; c <= c1; ++c) {
             const int64_t g = (rpb + c - 1) / c;
             const int64_t rounds = (base * c + 255) / 256, per = (g + kRqWaves / k - 1) / (kRqWaves / k);
+            if (best >= 0 && rounds * ((nqt + k - 1) / k + 6) >= best) break;  // (nor can more chunks be cheaper)
             const int64_t cost = rounds * (per * ((nqt + k - 1) / k) + 6);
             if (best < 0 || cost < best) { best = cost; bc = c; bk = k; }
         }
